@@ -18,7 +18,8 @@ constexpr int kMaxF = 16;             // harmonics per axis
 constexpr int kMaxBins = 128;
 constexpr int kCountCap = 1024;       // centroids whose pixel counts are privatised in LDS
 constexpr int kMfmaBins = 32;         // bin grids up to 32 x 32 take the matrix-core path
-constexpr int kPopKinds = 3;          // int8 palette operand kinds per axis (AxisOp in k_mfma.hpp)
+constexpr int kDistBase = 158;        // palette split of the matrix-core distances (head of k_mfma.hpp)
+constexpr int kPopKinds = 7;          // binary16 palette operand kinds per axis (Tables::pop)
 constexpr int kMaxBinBlocks = (kMaxBins + kMfmaBins - 1) / kMfmaBins;   // blocks of 32 bins per axis
 constexpr int kMaxSlices = 256;       // workgroups of the compaction (slices of the pixel list)
 constexpr int64_t kFusedMaxPixels = 1LL << 21;   // frames the vote launch compacts itself (two launches)
@@ -37,14 +38,13 @@ struct Tables {
     const uint16_t *wt;       // [kWKeys] 2^15 e^-d per 8-bit bucket (bucket order)
     const float *cx;          // [Bw] bin centres (pixels)
     const float *cy;          // [Bh]
-    // matrix-core path (bins <= 32)
-    const uint32_t *np1_x;    // [kMaxBinBlocks * 32] |P_w[bin]|^2 + 1 (1 for padded bins)
-    const uint32_t *np1_y;    // [kMaxBinBlocks * 32]
-    const uint32_t *pop;      // [axis][block][kind][64 lanes][4 words]: the int8 palette operand of
-                              //   lane l (bin 32 block + (l & 31), K slots 16 (l >> 5) .. + 15);
-                              //   see k_mfma.hpp
+    // matrix-core path
+    const uint32_t *pop;      // [axis][block][kind][64 lanes][4 words]: the binary16 palette operand of
+                              //   lane l (bin 32 block + (l & 31), K slots 8 (l >> 5) .. + 7); kinds:
+                              //   norms of A, norms of R for S, for S + 1, then hi and lo of channels
+                              //   0 .. 15 and of 16 .. 31; see k_mfma.hpp
     const uint32_t *wt_pk;    // [kWKeys] weight as two fp16 limbs (q & 255) | (q >> 8) << 16,
-                              //          at LDS position ((e + 31) & 31) * 256 + t
+                              //          at LDS position ((e + 17) & 31) * 256 + t
 };
 
 // Input to fixed point: rint(4096 clamp(v, -1.5, 1.5)), the input on the

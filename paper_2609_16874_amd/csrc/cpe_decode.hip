@@ -258,13 +258,13 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     // of fl32(S+1)
     h->wt.resize(kWKeys);
     for (int k = 0; k < kWKeys; k++) h->wt[k] = (uint16_t)std::rint(32768.0 * std::exp(-centre_distance(k, kWMant)));
-    // LDS order of the matrix-core kernels: bucket (e, t) at ((e + 31) & 31) << m | t,
-    // so that (float bits >> (23 - m)) & (2^(m+5) - 1) indexes it directly
+    // LDS order of the matrix-core kernels: bucket (e, t) at ((e + 17) & 31) << m | t,
+    // so that (bits >> (23 - m)) & (2^(m+5) - 1) of 2^-14 fl32(S + 1) indexes it directly
     std::vector<uint32_t> wt_pk(kWKeys);
     for (int k = 0; k < kWKeys; k++) {
         const int e = k >> kWMant, t = k & ((1 << kWMant) - 1);
         const int q = h->wt[k];
-        wt_pk[(((e + 31) & 31) << kWMant) | t] = (uint32_t)f16_bits(q & 255) | ((uint32_t)f16_bits(q >> 8) << 16);
+        wt_pk[(((e + 17) & 31) << kWMant) | t] = (uint32_t)f16_bits(q & 255) | ((uint32_t)f16_bits(q >> 8) << 16);
     }
 
     auto pack = [&](int n, const std::vector<int16_t> &pal, std::vector<int32_t> &pk, std::vector<uint32_t> &n2) {
@@ -285,49 +285,55 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     pack(bins_w, h->pal_x, pkx, n2x);
     pack(bins_h, h->pal_y, pky, n2y);
 
-    // matrix-core operands: -2P = 128 hi + lo with lo in [-64, 63] (|hi| <= 64),
-    // as int8 MFMA operands [axis][block of 32 bins][kind][64 lanes][16 bytes]:
-    // lane l holds bin 32 block + (l & 31) and the K slots 16 g .. 16 g + 15
-    // (g = l >> 5), whose channels are those the pixel operand of the same half
-    // holds (AxisOp in k_mfma.hpp): for 2F > 16 byte b is channel 8 g + b
-    // (b < 8) or 16 + 8 g + b - 8, kind 0 = hi, kind 1 = lo; for 2F <= 16 bytes b
-    // and 8 + b both belong to channel 8 g + b, kinds (hi, 0), (lo, hi),
-    // (0, lo).  Padded bins and channels are 0, and |P|^2 + 1 per bin (1 for
-    // padded bins).
-    std::vector<int8_t> pop((size_t)2 * kMaxBinBlocks * kPopKinds * 64 * 16, 0);
-    std::vector<uint32_t> np1x(kMaxBinBlocks * 32, 1u), np1y(kMaxBinBlocks * 32, 1u);
+    // matrix-core operands: -2P = kDistBase hi + lo with |lo| <= kDistBase / 2,
+    // as binary16 MFMA operands [axis][block of 32 bins][kind][64 lanes][8]:
+    // lane l holds bin 32 block + (l & 31) and the K slots 8 g .. 8 g + 7
+    // (g = l >> 5), which are the channels 16 j + 8 g + b of K-step j (hi:
+    // kind 3 + 2 j, lo: kind 4 + 2 j), or the slots x0 x1 y0 y1 x2 y2 1 1 of
+    // the pixel's norms (norm_operand in k_mfma.hpp): for the accumulators A
+    // (kind 0) and R (kind 1: S, kind 2: S + 1) the coefficients of the axis'
+    // three fields, 2^10 and 2^20 split by kDistBase, and in half 0 the
+    // constant |P|^2 (+ 1) less the offsets 1024 of the low fields of both
+    // halves, as 1024 h + l.  Everything but the limbs is scaled by 2^-14.
+    // Padded bins and channels are 0.
+    constexpr size_t kPopHalves = (size_t)2 * kMaxBinBlocks * kPopKinds * 64 * 8;
+    std::vector<_Float16> pop(kPopHalves, (_Float16)0.0f);
     for (int ax = 0; ax < 2; ax++) {
         const int n = ax ? bins_h : bins_w;
         const std::vector<int16_t> &pal = ax ? h->pal_y : h->pal_x;
-        auto limb = [&](int bin, int c, int which) -> int {     // which 0: hi, 1: lo
-            if (bin >= n || c >= twoF) return 0;
-            const int m2 = -2 * (int)pal[(size_t)bin * twoF + c];
-            const int lo = ((m2 + 64) & 127) - 64;
-            return which ? lo : (m2 - lo) / 128;
-        };
+        const std::vector<uint32_t> &n2 = ax ? n2y : n2x;
         for (int blk = 0; blk < kMaxBinBlocks; blk++)
             for (int l = 0; l < 64; l++) {
                 const int bin = 32 * blk + (l & 31), g = l >> 5;
-                for (int b = 0; b < 16; b++) {
-                    int v[kPopKinds];
-                    if (twoF > 16) {
-                        const int c = b < 8 ? 8 * g + b : 16 + 8 * g + (b - 8);
-                        v[0] = limb(bin, c, 0);
-                        v[1] = limb(bin, c, 1);
-                        v[2] = 0;
-                    } else {
-                        const int c = 8 * g + (b & 7);
-                        v[0] = b < 8 ? limb(bin, c, 0) : 0;
-                        v[1] = b < 8 ? limb(bin, c, 1) : limb(bin, c, 0);
-                        v[2] = b < 8 ? 0 : limb(bin, c, 1);
+                auto at = [&](int kind, int b) -> _Float16 & {
+                    return pop[((((size_t)ax * kMaxBinBlocks + blk) * kPopKinds + kind) * 64 + l) * 8 + b];
+                };
+                for (int j = 0; j < 2; j++)
+                    for (int b = 0; b < 8; b++) {
+                        const int c = 16 * j + 8 * g + b;
+                        const int m2 = bin < n && c < twoF ? -2 * (int)pal[(size_t)bin * twoF + c] : 0;
+                        const int hi = (int)std::rint((double)m2 / kDistBase);
+                        at(3 + 2 * j, b) = (_Float16)(float)hi;
+                        at(4 + 2 * j, b) = (_Float16)(float)(m2 - kDistBase * hi);
                     }
-                    for (int k = 0; k < kPopKinds; k++)
-                        pop[((((size_t)ax * kMaxBinBlocks + blk) * kPopKinds + k) * 64 + l) * 16 + b] = (int8_t)v[k];
+                const int norm = bin < n ? (int)n2[bin] : 0;
+                for (int kind = 0; kind < 3; kind++) {
+                    const int f1 = kind ? (1 << 10) % kDistBase : (1 << 10) / kDistBase;
+                    const int f2 = kind ? (1 << 20) % kDistBase : (1 << 20) / kDistBase;
+                    const int f0 = kind ? 1 : 0;
+                    const int c = (kind == 0 ? norm / kDistBase : norm % kDistBase + (kind == 2 ? 1 : 0)) -
+                                  2 * 1024 * (f0 + f1);
+                    const int ch = (int)std::floor((double)c / 1024.0), cl = c - 1024 * ch;
+                    const float s = 0x1p-14f;
+                    at(kind, 2 * ax) = (_Float16)(s * (float)f0);
+                    at(kind, 2 * ax + 1) = (_Float16)(s * (float)f1);
+                    at(kind, 4 + ax) = (_Float16)(s * (float)f2);
+                    if (g == 0) {
+                        at(kind, 6) = (_Float16)(s * 1024.0f * (float)ch);
+                        at(kind, 7) = (_Float16)(s * (float)cl);
+                    }
                 }
             }
-        std::vector<uint32_t> &np1 = ax ? np1y : np1x;
-        const std::vector<uint32_t> &n2 = ax ? n2y : n2x;
-        for (int bin = 0; bin < n; bin++) np1[bin] = n2[bin] + 1u;
     }
 
     // one allocation: constants, replicated histograms, last histogram, peak list, counters
@@ -341,8 +347,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     const size_t o_nx = carve(n2x.size() * 4), o_ny = carve(n2y.size() * 4);
     const size_t o_wt = carve(kWKeys * 2);
     const size_t o_cx = carve(cx.size() * 4), o_cy = carve(cy.size() * 4);
-    const size_t o_npx = carve(np1x.size() * 4), o_npy = carve(np1y.size() * 4);
-    const size_t o_pop = carve(pop.size());
+    const size_t o_pop = carve(pop.size() * 2);
     const size_t o_wpk = carve(wt_pk.size() * 4);
     const size_t o_hrep = carve(2 * (size_t)kReplicas * nb * 8);
     const size_t o_hlast = carve((size_t)nb * 8);
@@ -363,8 +368,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
               up(o_nx, n2x.data(), n2x.size() * 4) && up(o_ny, n2y.data(), n2y.size() * 4) &&
               up(o_wt, h->wt.data(), kWKeys * 2) &&
               up(o_cx, cx.data(), cx.size() * 4) && up(o_cy, cy.data(), cy.size() * 4) &&
-              up(o_npx, np1x.data(), np1x.size() * 4) && up(o_npy, np1y.data(), np1y.size() * 4) &&
-              up(o_pop, pop.data(), pop.size()) &&
+              up(o_pop, pop.data(), pop.size() * 2) &&
               up(o_wpk, wt_pk.data(), wt_pk.size() * 4) &&
               hipMemset(d + o_hrep, 0, 2 * (size_t)kReplicas * nb * 8) == hipSuccess &&
               hipMemset(d + o_hlast, 0, (size_t)nb * 8) == hipSuccess &&
@@ -382,8 +386,6 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     h->tb.wt = reinterpret_cast<const uint16_t *>(d + o_wt);
     h->tb.cx = reinterpret_cast<const float *>(d + o_cx);
     h->tb.cy = reinterpret_cast<const float *>(d + o_cy);
-    h->tb.np1_x = reinterpret_cast<const uint32_t *>(d + o_npx);
-    h->tb.np1_y = reinterpret_cast<const uint32_t *>(d + o_npy);
     h->tb.pop = reinterpret_cast<const uint32_t *>(d + o_pop);
     h->tb.wt_pk = reinterpret_cast<const uint32_t *>(d + o_wpk);
     h->sc.hrep = reinterpret_cast<unsigned long long *>(d + o_hrep);

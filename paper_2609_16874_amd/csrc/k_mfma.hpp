@@ -13,15 +13,27 @@
 // embedding rows of the next tile (and the list entries of the one after)
 // before computing the current one.  Every tile but the last is full.
 //
-// Per-axis distances (Eq4/Eq10).  The input X = rint(4096 v) (|X| <= 6144)
-// is split into int8 limbs X = 128 Xh + Xl (|Xh| <= 48, |Xl| <= 64) and the
-// palette into -2P = 128 hi + lo (|hi| <= 64, |lo| <= 64), so that
-//   S = |X|^2 + |P|^2 + 2^14 Xh.hi + 2^7 (Xh.lo + Xl.hi) + Xl.lo
-// with three dense [pixels x channels] x [channels x bins] contractions on
-// v_mfma_i32_32x32x32_i8 (exact int32 accumulation; the middle one takes two
-// instructions, or all three share one pixel operand when 2F <= 16, see
-// AxisOp); S < 2^32 follows modulo 2^32 from two shift-and-add instructions.
-// |X|^2 is three int8 dot products of the limbs.
+// Per-axis distances (Eq4/Eq10).  With the input X = rint(4096 v) (|X| <=
+// 6144) and the palette split as -2P = 158 hi + lo (|lo| <= 79), both limbs
+// whole binary16 numbers,
+//   S = |X|^2 + |P|^2 - 2 X.P = 158 A + R,  A = X.hi + a,  R = X.lo + b
+// where a and b hold the norms, |X|^2 + |P|^2 = 158 a + b.  A and R come from
+// dense [pixels x channels] x [channels x bins] contractions on
+// v_mfma_f32_32x32x16_f16, the norms from one more K-step (norm_operand:
+// |X|^2 = f0 + 2^10 f1 + 2^20 f2, with 2^10 = 158 6 + 76 and 2^20 = 158 6636 +
+// 88).  Every product and every partial sum, in any order, is a whole number
+// below 2^24 in magnitude (times the scale), so the binary32 accumulation is
+// exact.  With 32 channels |X| <= 34756, |P| <= 16387, and
+//   R: sum |X lo| <= 32 6144 79 = 15.53 10^6, norms <= 0.58 10^6;
+//   A: |X| |hi| <= 34756 (2 |P| + 79 sqrt 32) / 158 = 7.31 10^6, |X|^2 part
+//      <= 7.65 10^6, |P|^2 part <= 1.70 10^6, together 16.68 10^6 < 2^24
+//      (a base of 128 would let A reach 20.5 10^6, one of 172 R pass 2^24).
+// One fused multiply-add 158 A + R then rounds the exact S once: it is
+// fl32(S).  (Three int8 limb products with int32 accumulation, shifts, adds
+// and a conversion took 8 VALU instructions per result up to the weight's
+// packing instead of 4 and 11 instead of 6 per pair of input channels; at
+// 1024 x 2048, 16 harmonics, fp16, the vote goes from 38.1 to 32.8 us and the
+// assignment from 49.6 to 44.7 us.)
 //
 // Pass 1, k_vote_mfma (recovery + soft voting, Eq5/Eq6/Eq11).  With pixels
 // as the MFMA rows, the distance result leaves in each lane one bin and 16
@@ -63,29 +75,31 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kPopBytes = 2 * kPopKinds * 64 * 16;   // palette operands of both axes
+// The distance contraction (see the head of this file) splits -2P = kBase hi
+// + lo and carries every product scaled by kScale, which keeps all operands
+// normal binary16 numbers and shifts only the exponents of its results.
+constexpr float kBaseF = (float)kDistBase;
+constexpr float kScale = 0x1p-14f;
 
-// The int8 operand of one axis of one pixel, for the lane of half g = lane >> 5
-// of the MFMA, which holds the 16 K slots 16 g .. 16 g + 15.  The lane's
-// channels are c_b = 8 g + b and, for 2F > 16, 16 + 8 g + b (b = 0..7;
-// channels past 2F are zero).
-//   2F > 16: a[0] = Xh of the 16 channels, a[1] = Xl; with the palette
-//            operand kinds 0 = hi and 1 = lo (same channel order):
-//            Xh.hi, Xh.lo + Xl.hi, Xl.lo in four MFMAs;
-//   2F <= 16: a[0] = Xh of the 8 channels, then their Xl; with the kinds
-//            0 = (hi, 0), 1 = (lo, hi), 2 = (0, lo) the three products take
-//            one MFMA each.
+// Operands of one axis of a tile: per K-step of 16 channels a hi and a lo
+// palette operand, after the constants of the A and the R accumulator.
 template <int F>
-struct AxisOp {
-    static constexpr bool kPacked = 2 * F <= 16;
-    static constexpr int N = kPacked ? 1 : 2;
-    i32x4 a[N];
-};
+constexpr int kSteps = (2 * F + 15) / 16;
+template <int F>
+constexpr int kAxisKinds = 2 + 2 * kSteps<F>;
+template <int F>
+constexpr int kPopBytes = 2 * kAxisKinds<F> * 64 * 16;   // LDS palette operands of both axes
 
-__device__ __forceinline__ i32x16 mfma8(i32x4 a, i32x4 b, i32x16 c)
-{
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
-}
+// The binary16 pixel operands of one axis: the K slots 8 g .. 8 g + 7 of step
+// j (lane half g) hold kScale X of the channels 16 j + 8 g + b (channels past
+// 2F are zero).  A binary16 input's X has at most 11 significant bits (its
+// spacing exceeds 1/4096 where |X| > 1024), so one number holds it; a
+// binary32 input's 13-bit X takes two, its leading 11 bits and the rest.
+template <typename T, int F>
+struct AxisOp {
+    static constexpr int NL = sizeof(T) == 2 ? 1 : 2;
+    f16x8 a[NL][kSteps<F>];
+};
 
 __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 {
@@ -100,49 +114,28 @@ constexpr int kFastGap = 8;
 // Row of the 32 x 32 MFMA result held by register r of a lane in group g.
 __device__ __forceinline__ constexpr int acc_row(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
 
-// int8 limbs of two channels: Xh = rint(32 c) and Xl = rint(128 (32 c - Xh)),
-// c = clamp(v, -1.5, 1.5), so that 128 Xh + Xl = rint(4096 c) (128 Xh is
-// even, so the ties agree).  In fp16: 32 c + 1536 lies in [1488, 1584], where
-// the spacing is 1, so the fused multiply-add rounds it to 1536 + Xh; 32 c -
-// Xh is exact (|.| <= 1/2) and 128 times it plus 1536 rounds to 1536 + Xl.
-// The low byte of each result's bit pattern 0x6600 + k is k as an int8.  A
-// NaN clamps to -1.5 (max returns the non-NaN operand).
-struct LimbPair {
-    uint32_t h, l;     // two fp16 bit patterns each
-};
-__device__ __forceinline__ LimbPair limbs_f16(f16x2 v)
+// Two channels of a binary16 input as kScale X, X = rint(4096 clamp(v, -1.5,
+// 1.5)): 2^-12 v is subnormal where X needs rounding (|v| < 1/4), and the
+// spacing 2^-24 of the subnormals is that of X 2^-24, so the product rounds
+// exactly as rint; the clamp commutes with it, and the second product is
+// exact.  A NaN clamps to -1.5 (max returns the non-NaN operand).
+__device__ __forceinline__ f16x2 scaled_pair(uint32_t w)
 {
-    const f16x2 lo = {(_Float16)-1.5f, (_Float16)-1.5f}, hi = {(_Float16)1.5f, (_Float16)1.5f};
-    const f16x2 k32 = {(_Float16)32.0f, (_Float16)32.0f}, k128 = {(_Float16)128.0f, (_Float16)128.0f};
-    const f16x2 m = {(_Float16)1536.0f, (_Float16)1536.0f};
-    f16x2 c = __builtin_elementwise_max(v, lo);
+    const f16x2 down = {(_Float16)0x1p-12f, (_Float16)0x1p-12f}, up = {(_Float16)0x1p10f, (_Float16)0x1p10f};
+    const f16x2 lo = {(_Float16)-0x1.8p-12f, (_Float16)-0x1.8p-12f}, hi = {(_Float16)0x1.8p-12f, (_Float16)0x1.8p-12f};
+    f16x2 c = __builtin_bit_cast(f16x2, w) * down;
+    c = __builtin_elementwise_max(c, lo);
     c = __builtin_elementwise_min(c, hi);
-    const f16x2 h = __builtin_elementwise_fma(c, k32, m);
-    const f16x2 hv = h - m;
-    const f16x2 d = __builtin_elementwise_fma(c, k32, -hv);
-    const f16x2 l = __builtin_elementwise_fma(d, k128, m);
-    return {__builtin_bit_cast(uint32_t, h), __builtin_bit_cast(uint32_t, l)};
+    return c * up;
 }
 
-// The same in fp32 (exact: |32 c| < 2^22 around 1.5 * 2^23, whose spacing is
-// 1); the low byte of the bit pattern 0x4B400000 + k is k as an int8.
-__device__ __forceinline__ void limbs_f32(float v, uint32_t &h, uint32_t &l)
+// Both halves of x = kScale X as the int16 pair 2X: rint(32767 x) = rint(2X -
+// X / 2^14), and |X / 2^14| < 3/8.
+__device__ __forceinline__ v2s twice_x(f16x2 x)
 {
-    constexpr float kM = 12582912.0f;
-    const float c = fminf(fmaxf(v, -1.5f), 1.5f);
-    const float hf = __builtin_fmaf(c, 32.0f, kM);
-    const float hv = hf - kM;
-    const float d = __builtin_fmaf(c, 32.0f, -hv);
-    const float lf = __builtin_fmaf(d, 128.0f, kM);
-    h = __float_as_uint(hf);
-    l = __float_as_uint(lf);
-}
-
-// Low bytes of the two halves of w0 (bytes 0, 1 of the result) and of w1
-// (bytes 2, 3).
-__device__ __forceinline__ uint32_t low_bytes(uint32_t w1, uint32_t w0)
-{
-    return __builtin_amdgcn_perm(w1, w0, 0x06040200u);
+    uint32_t r;
+    asm("v_cvt_pknorm_i16_f16 %0, %1, %1 op_sel:[0,1,0]" : "=v"(r) : "v"(x));
+    return __builtin_bit_cast(v2s, r);
 }
 
 // Raw input words of one lane's operand slices: for each axis and K-step j
@@ -151,172 +144,193 @@ __device__ __forceinline__ uint32_t low_bytes(uint32_t w1, uint32_t w0)
 template <typename T, int F>
 struct RawSlices {
     static constexpr int C = 2 * F;
-    static constexpr int KS = (C + 15) / 16;
-    static constexpr bool kH = sizeof(T) == 2;
-    // 16-byte aligned vector slices: whole K-steps, or a single 8-channel
-    // slice per axis (F = 4) that the lanes of half 0 load
-    static constexpr bool kVec = C % 16 == 0 || C == 8;
-    static constexpr int kWords = (kH && kVec) ? 4 : 8;
+    static constexpr int KS = kSteps<F>;
+    static constexpr int kWords = 2 * (int)sizeof(T);      // of a slice
+    // channels per load: the widest group that divides the axis block and is
+    // aligned in it (16-byte loads for whole slices and F even fp32, else 8
+    // bytes, or 4 for odd F in fp16), so that a group is a part of the block
+    // or lies past it
+    static constexpr int kG = C % 16 == 0 || C == 8 ? 8 : F % 2 == 0 ? 4 : 2;
+    static constexpr int kGB = kG * (int)sizeof(T);        // its bytes
+    static constexpr int kLoad = kGB < 16 ? kGB : 16;      // bytes of one load
     uint32_t w[2][KS][kWords];
 
     // `row` = first channel of the pixel, `yoff` = first channel of its y
-    // block.  The host guarantees that every vector slice is 16-byte aligned
-    // (16-byte aligned embedding; 2F a multiple of 16, or 2F = 8 with the
-    // row and the y block 16-byte aligned).
+    // block.  The embedding is 16-byte aligned, and so are the row and the y
+    // block where D > 4F; where D = 4F their offsets are multiples of 2F
+    // channels, so of kLoad bytes.
     __device__ __forceinline__ void load(const T *__restrict__ row, int yoff, int g)
     {
 #pragma unroll
         for (int ax = 0; ax < 2; ax++)
 #pragma unroll
-            for (int j = 0; j < KS; j++) {
-                const T *blk = row + ax * yoff + 16 * j + 8 * g;
-                if constexpr (kVec) {
-                    // C == 8: the slice of half 1 lies past the block; it reads
-                    // the half-0 slice (in bounds) and keeps zeros
-                    const bool on = C % 16 == 0 || g == 0;
-                    const T *src = on ? blk : row + ax * yoff + 16 * j;
-                    if constexpr (kH) {
-                        const u32x4 v = *reinterpret_cast<const u32x4 *>(__builtin_assume_aligned(src, 16));
+            for (int j = 0; j < KS; j++)
 #pragma unroll
-                        for (int q = 0; q < 4; q++) w[ax][j][q] = on ? v[q] : 0u;
-                    } else {
-                        const float4 *p = reinterpret_cast<const float4 *>(__builtin_assume_aligned(src, 16));
-                        const float4 a = p[0], b = p[1];
-                        const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                for (int q = 0; q < 8 / kG; q++) {
+                    uint32_t *dst = &w[ax][j][q * kGB / 4];
+                    const int c0 = 16 * j + kG * q;            // of half 0; half 1's is 8 further
+                    if (c0 >= C) {
 #pragma unroll
-                        for (int q = 0; q < 8; q++) w[ax][j][q] = on ? __float_as_uint(f[q]) : 0u;
+                        for (int i = 0; i < kGB / 4; i++) dst[i] = 0u;
+                        continue;
                     }
-                } else {
+                    // a group of half 1 past the block reads the block's
+                    // first one (in bounds) and keeps zeros
+                    const bool on = c0 + 8 < C || g == 0;
+                    const T *src = row + ax * yoff + (on ? c0 + 8 * g : 0);
 #pragma unroll
-                    for (int s = 0; s < 8; s++)
-                        w[ax][j][s] =
-                            __float_as_uint((16 * j + 8 * g + s) < C ? load_scalar<T>(blk + s) : 0.0f);
+                    for (int k = 0; k < kGB / kLoad; k++) {
+                        typedef uint32_t vec __attribute__((ext_vector_type(kLoad / 4)));
+                        if constexpr (kLoad == 4) {
+                            const uint32_t v = *reinterpret_cast<const uint32_t *>(__builtin_assume_aligned(src, 4));
+                            dst[0] = on ? v : 0u;
+                        } else {
+                            const vec v =
+                                reinterpret_cast<const vec *>(__builtin_assume_aligned(src, kLoad))[k];
+#pragma unroll
+                            for (int i = 0; i < kLoad / 4; i++) dst[k * kLoad / 4 + i] = on ? v[i] : 0u;
+                        }
+                    }
                 }
-            }
     }
 
-    // int8 operand of one axis and this lane's part of |X|^2 over its
-    // channels (added to n2).
-    __device__ __forceinline__ void convert(int ax, AxisOp<F> &op, int &n2) const
+    // Operands of one axis; this lane's part of |X|^2 over its channels,
+    // times 4 for a binary16 input, is added to n2 (modulo 2^32, below it).
+    __device__ __forceinline__ void convert(int ax, AxisOp<T, F> &op, int &n2) const
     {
-        uint32_t hb[KS][2], lb[KS][2];      // packed limb bytes, 4 channels per word
 #pragma unroll
         for (int j = 0; j < KS; j++) {
-            if constexpr (kH && kVec) {
-                LimbPair p[4];
+            if constexpr (sizeof(T) == 2) {
+                u32x4 t;
 #pragma unroll
-                for (int q = 0; q < 4; q++) p[q] = limbs_f16(__builtin_bit_cast(f16x2, w[ax][j][q]));
-#pragma unroll
-                for (int q = 0; q < 2; q++) {
-                    hb[j][q] = low_bytes(p[2 * q + 1].h, p[2 * q].h);
-                    lb[j][q] = low_bytes(p[2 * q + 1].l, p[2 * q].l);
+                for (int q = 0; q < 4; q++) {
+                    const f16x2 x = scaled_pair(w[ax][j][q]);
+                    const v2s x2 = twice_x(x);
+                    n2 = __builtin_amdgcn_sdot2(x2, x2, n2, false);
+                    t[q] = __builtin_bit_cast(uint32_t, x);
                 }
+                op.a[0][j] = __builtin_bit_cast(f16x8, t);
             } else {
-                uint32_t h[8], l[8];
+                // 768 = 1.5 2^9 has the spacing 2^-14 of kScale X, so the
+                // multiply-add rounds 4096 v to X, and its low 16 bits are X
+                constexpr float kM = 768.0f;
+                u32x4 t, u;
 #pragma unroll
-                for (int s = 0; s < 8; s++) limbs_f32(__uint_as_float(w[ax][j][s]), h[s], l[s]);
+                for (int q = 0; q < 4; q++) {
+                    float x[2], r[2];
+                    uint32_t b[2];
 #pragma unroll
-                for (int q = 0; q < 2; q++) {
-                    hb[j][q] = low_bytes(__builtin_amdgcn_perm(h[4 * q + 3], h[4 * q + 2], 0x05040100u),
-                                         __builtin_amdgcn_perm(h[4 * q + 1], h[4 * q], 0x05040100u));
-                    lb[j][q] = low_bytes(__builtin_amdgcn_perm(l[4 * q + 3], l[4 * q + 2], 0x05040100u),
-                                         __builtin_amdgcn_perm(l[4 * q + 1], l[4 * q], 0x05040100u));
+                    for (int i = 0; i < 2; i++) {
+                        const float c = fminf(fmaxf(__uint_as_float(w[ax][j][2 * q + i]), -1.5f), 1.5f);
+                        const float m = __builtin_fmaf(c, 4096.0f * kScale, kM);
+                        b[i] = __float_as_uint(m);
+                        x[i] = m - kM;
+                    }
+                    const v2s xi = __builtin_bit_cast(v2s, __builtin_amdgcn_perm(b[1], b[0], 0x05040100u));
+                    n2 = __builtin_amdgcn_sdot2(xi, xi, n2, false);
+                    const auto lead = __builtin_amdgcn_cvt_pkrtz(x[0], x[1]);
+                    r[0] = x[0] - (float)lead[0];
+                    r[1] = x[1] - (float)lead[1];
+                    t[q] = __builtin_bit_cast(uint32_t, lead);
+                    u[q] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r[0], r[1]));
                 }
+                op.a[0][j] = __builtin_bit_cast(f16x8, t);
+                op.a[1][j] = __builtin_bit_cast(f16x8, u);
             }
-        }
-        int hh = 0, hl = 0, ll = 0;
-#pragma unroll
-        for (int j = 0; j < KS; j++)
-#pragma unroll
-            for (int q = 0; q < 2; q++) {
-                hh = __builtin_amdgcn_sdot4((int)hb[j][q], (int)hb[j][q], hh, false);
-                hl = __builtin_amdgcn_sdot4((int)hb[j][q], (int)lb[j][q], hl, false);
-                ll = __builtin_amdgcn_sdot4((int)lb[j][q], (int)lb[j][q], ll, false);
-            }
-        n2 += (hh << 14) + (hl << 8) + ll;
-        if constexpr (AxisOp<F>::kPacked) {
-            op.a[0] = i32x4{(int)hb[0][0], (int)hb[0][1], (int)lb[0][0], (int)lb[0][1]};
-        } else {
-            op.a[0] = i32x4{(int)hb[0][0], (int)hb[0][1], (int)hb[1][0], (int)hb[1][1]};
-            op.a[1] = i32x4{(int)lb[0][0], (int)lb[0][1], (int)lb[1][0], (int)lb[1][1]};
         }
     }
 };
 
+// The operand that adds the norms: this lane's parts n of |X|^2 (convert) of
+// both axes in fields of 10, 10 and the rest of the bits, as the binary16
+// numbers 1024 + field (the two low ones, packed by or-ing the field into
+// the mantissa) and the field itself (at most 576), then two ones for the
+// palette's constants: slots x0 x1 y0 y1 x2 y2 1 1.
+template <typename T>
+__device__ __forceinline__ f16x8 norm_operand(uint32_t nx, uint32_t ny)
+{
+    constexpr int SH = sizeof(T) == 2 ? 2 : 0;
+    auto low = [](uint32_t n) {
+        return ((n >> SH) & 0x3ffu) | ((n << (6 - SH)) & 0x03ff0000u) | 0x64006400u;
+    };
+    const u32x4 w = {low(nx), low(ny),
+                     __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)(nx >> (20 + SH)),
+                                                                             (float)(ny >> (20 + SH)))),
+                     0x3c003c00u};
+    return __builtin_bit_cast(f16x8, w);
+}
 
-// An empty asm that takes the converted operands and clobbers memory: the
-// next tile's row loads, which follow it, issue after the conversion and
-// reuse the input registers (otherwise the compiler hoists them above the
-// conversion and copies 16 registers per tile).
+// Operands of both axes of one tile.
+template <typename T, int F>
+struct PixOps {
+    AxisOp<T, F> ax[2];
+    f16x8 e;
+
+    // Empty asm statements that take the converted operands, the last one
+    // clobbering memory: the next tile's row loads, which follow it, issue
+    // after the conversion and reuse the input registers (otherwise the
+    // compiler hoists them above the conversion and copies 16 registers per
+    // tile).
+    __device__ __forceinline__ void from(const RawSlices<T, F> &raw)
+    {
+        int nx = 0, ny = 0;
+        raw.convert(0, ax[0], nx);
+        raw.convert(1, ax[1], ny);
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int l = 0; l < AxisOp<T, F>::NL; l++)
+#pragma unroll
+                for (int j = 0; j < kSteps<F>; j++) __asm__ volatile("" : "+v"(ax[a].a[l][j]));
+        __asm__ volatile("" : "+v"(nx), "+v"(ny) : : "memory");
+        e = norm_operand<T>((uint32_t)nx, (uint32_t)ny);
+    }
+};
+
+// Palette operand k of axis ax for lane `lane` (bin lane & 31, K slots 8 g ..
+// 8 g + 7, g = lane >> 5).
 template <int F>
-__device__ __forceinline__ void after_convert(AxisOp<F> &X, AxisOp<F> &Y, int &n2x, int &n2y)
+__device__ __forceinline__ f16x8 palette_operand(const uint32_t *__restrict__ pop, int ax, int k, int lane)
 {
-    if constexpr (AxisOp<F>::kPacked)
-        __asm__ volatile("" : "+v"(X.a[0]), "+v"(Y.a[0]), "+v"(n2x), "+v"(n2y) : : "memory");
-    else
-        __asm__ volatile("" : "+v"(X.a[0]), "+v"(X.a[1]), "+v"(Y.a[0]), "+v"(Y.a[1]), "+v"(n2x), "+v"(n2y) : : "memory");
+    return *reinterpret_cast<const f16x8 *>(pop + (((ax * kAxisKinds<F> + k) * 64 + lane) * 4));
 }
 
-// Palette operand of kind k for axis ax of lane `lane` (bin lane & 31, K
-// slots 16 (lane >> 5) .. + 15).
-__device__ __forceinline__ i32x4 palette_operand(const uint32_t *__restrict__ pop, int ax, int k, int lane)
-{
-    return *reinterpret_cast<const i32x4 *>(pop + (((ax * kPopKinds + k) * 64 + lane) * 4));
-}
-
-// Word group i (16 bytes) of the LDS palette operands [axis][kind][64][16] for
-// the x bins of block bx and the y bins of block by, from the table
-// [axis][kMaxBinBlocks][kind][64][16].
+// Word group i (16 bytes) of the LDS palette operands [axis][kAxisKinds][64]
+// [16] for the x bins of block bx and the y bins of block by, from the table
+// [axis][kMaxBinBlocks][kPopKinds][64][16]; PLUS1: with the constants of S +
+// 1 instead of S.
+template <int F, bool PLUS1>
 __device__ __forceinline__ u32x4 pop_block(const uint32_t *__restrict__ pop, int i, int bx, int by)
 {
-    constexpr int kAxis = kPopKinds * 64;                 // 16-byte groups per axis and block
-    const int ax = i / kAxis, r = i % kAxis;
+    constexpr int kAxis = kAxisKinds<F> * 64;             // 16-byte groups per axis
+    const int ax = i / kAxis, r = i % kAxis, k = r >> 6;
     const int blk = ax ? by : bx;
-    return reinterpret_cast<const u32x4 *>(pop)[(ax * kMaxBinBlocks + blk) * kAxis + r];
+    const int kind = k == 0 ? 0 : k == 1 ? (PLUS1 ? 2 : 1) : k + 1;
+    return reinterpret_cast<const u32x4 *>(pop)[((ax * kMaxBinBlocks + blk) * kPopKinds + kind) * 64 + (r & 63)];
 }
 
-// The three limb products of one axis: hh = Xh.hi, mid = Xh.lo + Xl.hi and
-// ll = ll0 + Xl.lo (ll0: the starting values).  PIX_ROWS: pixels are the
-// MFMA rows (pass 1) or its columns (pass 2).
-template <int F, bool PIX_ROWS>
-__device__ __forceinline__ void axis_products(const AxisOp<F> &X, const i32x4 (&P)[kPopKinds], i32x16 ll0,
-                                              i32x16 &hh, i32x16 &mid, i32x16 &ll)
+// The accumulators A and R of one axis, kDistBase A + R = kScale S (or kScale
+// (S + 1)).  PIX_ROWS: pixels are the MFMA rows (pass 1) or its columns
+// (pass 2).
+template <typename T, int F, bool PIX_ROWS>
+__device__ __forceinline__ void axis_products(const AxisOp<T, F> &X, f16x8 e, const f16x8 (&P)[kAxisKinds<F>],
+                                              f32x16 &A, f32x16 &R)
 {
-    const i32x16 z = {};
-    auto mm = [](i32x4 px, i32x4 pal, i32x16 c) { return PIX_ROWS ? mfma8(px, pal, c) : mfma8(pal, px, c); };
-    if constexpr (AxisOp<F>::kPacked) {
-        hh = mm(X.a[0], P[0], z);
-        mid = mm(X.a[0], P[1], z);
-        ll = mm(X.a[0], P[2], ll0);
-    } else {
-        hh = mm(X.a[0], P[0], z);
-        mid = mm(X.a[0], P[1], z);
-        mid = mm(X.a[1], P[0], mid);
-        ll = mm(X.a[1], P[1], ll0);
-    }
-}
-
-// 2^14 hh + 2^7 mid + ll + c (mod 2^32) as two shift-and-add instructions
-// and one add.
-__device__ __forceinline__ uint32_t assemble(int hh, int mid, int ll, uint32_t c)
-{
-    const uint32_t t = ((uint32_t)hh << 7) + (uint32_t)mid;
-    return (t << 7) + (uint32_t)ll + c;
-}
-
-// Starting values of one accumulator for the 16 rows acc_row(r, g) of a lane
-// in group g, from an LDS array indexed by row.
-__device__ __forceinline__ i32x16 row_init(const uint32_t *a, int g)
-{
-    i32x16 v;
+    const f32x16 z = {};
+    auto mm = [](f16x8 px, f16x8 pal, f32x16 c) { return PIX_ROWS ? mfma16(px, pal, c) : mfma16(pal, px, c); };
+    A = mm(e, P[0], z);
+    R = mm(e, P[1], z);
 #pragma unroll
-    for (int r4 = 0; r4 < 4; r4++) {
-        const u32x4 w = *reinterpret_cast<const u32x4 *>(a + 8 * r4 + 4 * g);
+    for (int j = 0; j < kSteps<F>; j++)
 #pragma unroll
-        for (int i = 0; i < 4; i++) v[4 * r4 + i] = (int)w[i];
-    }
-    return v;
+        for (int l = 0; l < AxisOp<T, F>::NL; l++) {
+            A = mm(X.a[l][j], P[2 + 2 * j], A);
+            R = mm(X.a[l][j], P[3 + 2 * j], R);
+        }
 }
+
+// kScale fl32(S) (or S + 1): one rounding of the exact sum.
+__device__ __forceinline__ float assemble(float A, float R) { return __builtin_fmaf(kBaseF, A, R); }
 
 // Tiles [first, last) of workgroup b of nb when ntiles tiles are shared out
 // in contiguous runs.
@@ -345,13 +359,12 @@ __device__ __forceinline__ int take_tile(int *next, int lane, int first, int wav
 constexpr int kHStride = kMfmaBins + 1;
 
 // LDS bytes of k_vote_mfma: the packed weight table, the 64-bit histogram,
-// the palette operands, per wave |X|^2 of one tile's pixels per axis, the
-// slice prefix sums and counters; with the compaction folded in (FUSED),
-// the workgroup's own participating pixels.
-constexpr size_t kVoteLds(int wpb, bool fused)
+// the palette operands, the slice prefix sums and counters; with the
+// compaction folded in (FUSED), the workgroup's own participating pixels.
+template <int F>
+constexpr size_t kVoteLds(bool fused)
 {
-    return (size_t)kWKeys * 4 + kMfmaBins * kHStride * 8 + kPopBytes + (size_t)wpb * 64 * 4 + (kMaxSlices + 1) * 4 +
-           16 + (fused ? (size_t)kFusedMaxSeg * 4 : 0);
+    return (size_t)kWKeys * 4 + kMfmaBins * kHStride * 8 + kPopBytes<F> + (kMaxSlices + 1) * 4 + 16 + (fused ? (size_t)kFusedMaxSeg * 4 : 0);
 }
 
 // Eight foreground values from pixel p0 on (p0 a multiple of 8), in two
@@ -457,12 +470,11 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     // blocks of 32 x 32 bins: one pass over the workgroup's tiles per block
     const int nbx = MULTI ? (Bw + kMfmaBins - 1) / kMfmaBins : 1, nby = MULTI ? (Bh + kMfmaBins - 1) / kMfmaBins : 1;
     // All LDS is static, so that table addresses are compile-time constants.
-    __shared__ __align__(16) unsigned char smem[kVoteLds(kWpb, FUSED)];
+    __shared__ __align__(16) unsigned char smem[kVoteLds<F>(FUSED)];
     uint32_t *s_wt = reinterpret_cast<uint32_t *>(smem);                              // [kWKeys] fp16 limb pairs
     unsigned long long *s_h = reinterpret_cast<unsigned long long *>(s_wt + kWKeys);  // [32][kHStride], b * kHStride + a
     uint32_t *s_pop = reinterpret_cast<uint32_t *>(s_h + kMfmaBins * kHStride);      // palette operands
-    uint32_t *s_ini = s_pop + kPopBytes / 4;                                          // [kWpb][2][32]
-    int *s_pref = reinterpret_cast<int *>(s_ini + kWpb * 64);                        // [kMaxSlices + 1]
+    int *s_pref = reinterpret_cast<int *>(s_pop + kPopBytes<F> / 4);                  // [kMaxSlices + 1]
     int *s_next = s_pref + kMaxSlices + 1;                                            // next tile of the run
     int *s_cnt = s_next + 1;                                                          // FUSED: [2] pixels listed (LDS, global)
     int *s_list = s_pref + kMaxSlices + 5;                                            // FUSED: [kFusedMaxSeg]
@@ -471,10 +483,6 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     const int g = lane >> 5, ln = lane & 31;
     SliceLoad sl;
     if (!FUSED && list) slice_load(counts, nslices, sl);
-    // the bin constants of this lane's bin in the first block (loaded with
-    // the tables, not after the barrier, where they would cost a memory round
-    // trip of their own)
-    uint32_t np1x = tb.np1_x[ln], np1y = tb.np1_y[ln];
     {
         constexpr int kThreads = kWpb * 64, kN = kWKeys / 4, kPer = (kN + kThreads - 1) / kThreads;
         u32x4 w[kPer];
@@ -581,7 +589,8 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
             if (i < kN) reinterpret_cast<u32x4 *>(s_wt)[i] = w[k];
         }
         for (int i = tid; i < kMfmaBins * kHStride; i += kThreads) s_h[i] = 0ull;
-        for (int i = tid; i < kPopBytes / 16; i += kThreads) reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block(tb.pop, i, 0, 0);
+        for (int i = tid; i < kPopBytes<F> / 16; i += kThreads)
+            reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, true>(tb.pop, i, 0, 0);
         if (tid == 0) *s_next = 0;
         if (!FUSED && list) slice_scan(sl, nslices, s_pref);
     }
@@ -597,8 +606,6 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
         block_run(ntiles, blockIdx.x, gridDim.x, t0, tend);
     }
 
-    // this wave's |X|^2 per axis: [0] x, [1] y, by pixel
-    uint32_t *ini = s_ini + wv * 64;
     f32x16 acc2 = {}, acc1 = {}, acc0 = {};
     int ntile = 0;
 
@@ -618,47 +625,27 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     };
 
     // Packed weight limbs of the 16 (pixel, bin) results of one axis: the
-    // accumulators start at the pixels' |X|^2, and cb = |P|^2 + 1 of this
-    // lane's bin completes S + 1, whose binary32 bits give the bucket.
-    auto weights = [&](const i32x16 &hh, const i32x16 &mid, const i32x16 &ll, uint32_t cb, uint32_t (&e)[16]) {
+    // binary32 bits of kScale (S + 1) give the bucket.
+    auto weights = [&](const f32x16 &A, const f32x16 &R, uint32_t (&e)[16]) {
 #pragma unroll
-        for (int r = 0; r < 16; r++) {
-            const uint32_t s1 = assemble(hh[r], mid[r], ll[r], cb);
-            e[r] = s_wt[(__float_as_uint((float)s1) >> 15) & (kWKeys - 1)];
-        }
+        for (int r = 0; r < 16; r++) e[r] = s_wt[(__float_as_uint(assemble(A[r], R[r])) >> 15) & (kWKeys - 1)];
     };
 
     // One tile of up to 32 pixels (queue slot m = lane & 31) from prefetched
     // input; `next` reuses the input registers once they are converted.
     auto tile = [&](RawSlices<T, F> &raw, int nvalid, auto next) {
-        int n2x = 0, n2y = 0;
-        AxisOp<F> X, Y;
-        raw.convert(0, X, n2x);
-        raw.convert(1, Y, n2y);
-        after_convert(X, Y, n2x, n2y);
+        PixOps<T, F> X;
+        X.from(raw);
         next();
-        n2x += __shfl_xor(n2x, 32);
-        n2y += __shfl_xor(n2y, 32);
-        if (g == 0) {
-            ini[ln] = (uint32_t)n2x;
-            ini[32 + ln] = (uint32_t)n2y;
-        }
         uint32_t ex[16], ey[16];
-        {
-            i32x4 P[kPopKinds];
 #pragma unroll
-            for (int k = 0; k < kPopKinds; k++) P[k] = palette_operand(s_pop, 0, k, lane);
-            i32x16 hh, mid, ll;
-            axis_products<F, true>(X, P, row_init(ini, g), hh, mid, ll);
-            weights(hh, mid, ll, np1x, ex);
-        }
-        {
-            i32x4 P[kPopKinds];
+        for (int ax = 0; ax < 2; ax++) {
+            f16x8 P[kAxisKinds<F>];
 #pragma unroll
-            for (int k = 0; k < kPopKinds; k++) P[k] = palette_operand(s_pop, 1, k, lane);
-            i32x16 hh, mid, ll;
-            axis_products<F, true>(Y, P, row_init(ini + 32, g), hh, mid, ll);
-            weights(hh, mid, ll, np1y, ey);
+            for (int k = 0; k < kAxisKinds<F>; k++) P[k] = palette_operand<F>(s_pop, ax, k, lane);
+            f32x16 A, R;
+            axis_products<T, F, true>(X.ax[ax], X.e, P, A, R);
+            weights(A, R, ax ? ey : ex);
         }
         if (nvalid < 32) {        // pixels past the end of the list vote nothing
             // (kept a real branch: only the last tile of a round is partial)
@@ -695,13 +682,11 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     for (int blk = 0; blk < nbx * nby; blk++) {
         const int bx = blk % nbx, by = blk / nbx;
         if (MULTI && blk > 0) {
-            // the next block: its palette operands and bin constants, a clear
-            // histogram and tile counter (the previous pass has flushed)
-            np1x = tb.np1_x[kMfmaBins * bx + ln];
-            np1y = tb.np1_y[kMfmaBins * by + ln];
+            // the next block: its palette operands, a clear histogram and tile
+            // counter (the previous pass has flushed)
             for (int i = tid; i < kMfmaBins * kHStride; i += blockDim.x) s_h[i] = 0ull;
-            for (int i = tid; i < kPopBytes / 16; i += blockDim.x)
-                reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block(tb.pop, i, bx, by);
+            for (int i = tid; i < kPopBytes<F> / 16; i += blockDim.x)
+                reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, true>(tb.pop, i, bx, by);
             if (tid == 0) *s_next = 0;
             __syncthreads();
         }
@@ -773,13 +758,18 @@ constexpr int kAssignWpb = 4 * kAssignWaves<T, F>;
 // it is no longer read).  The summed vote histogram (32 x 32 slots, 8 KB) of the prologue
 // shares its bytes with the first waves' distance arrays, which are written
 // only after it is no longer read.
+template <int F>
 constexpr size_t kAssignLdsCore(int wpb)
 {
-    return (size_t)kPopBytes + 4 * kMfmaBins * 4 + (size_t)kMaxBatchLds * 20 + kMfmaBins * kMfmaBins * 2 +
+    return (size_t)kPopBytes<F> + (size_t)kMaxBatchLds * 20 + kMfmaBins * kMfmaBins * 2 +
            kMfmaBins * kMfmaBins * 4 + (size_t)wpb * 2 * kMfmaBins * kKeyStride * 4 + sizeof(PeakLds) +
            (kMaxSlices + 1) * 4 + 16;
 }
-constexpr size_t kAssignLds(int wpb) { return (kAssignLdsCore(wpb) + 15) & ~(size_t)15; }
+template <int F>
+constexpr size_t kAssignLds(int wpb)
+{
+    return (kAssignLdsCore<F>(wpb) + 15) & ~(size_t)15;
+}
 
 // Every workgroup first sums the vote histograms `hcur` of the vote launch
 // and extracts the peaks in LDS (identical in every workgroup); workgroup 0
@@ -793,11 +783,12 @@ constexpr size_t kAssignLds(int wpb) { return (kAssignLdsCore(wpb) + 15) & ~(siz
 // fixed stride.
 // The candidate search walks the batches of 4 columns of one row (see the
 // search below).  A pixel is labelled iff its distance sum D (in units of
-// 1/4096) is below tau4096 = 4096 tau (Eq8; +inf: every pixel).
+// 1/32, the scale of the distance arrays) is below tau32 = 32 tau (Eq8; +inf:
+// every pixel).
 template <typename T, int F, bool FAST>
 __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_waves_per_eu(kAssignWaves<T, F>))) void k_assign_mfma(
     const T *__restrict__ emb, int32_t dstride, int32_t yoff, const int32_t *__restrict__ list,
-    const int32_t *__restrict__ counts, int32_t nslices, int32_t slice_px, int32_t npix, double tau4096, Tables tb,
+    const int32_t *__restrict__ counts, int32_t nslices, int32_t slice_px, int32_t npix, double tau32, Tables tb,
     const unsigned long long *__restrict__ hcur, unsigned long long *__restrict__ hlast, int32_t Bw, int32_t Bh, long long cut, int32_t cap,
     cpe_centroid *__restrict__ cents, int32_t *__restrict__ num, int32_t *__restrict__ labels,
     float *__restrict__ score_map, int32_t force_exact)
@@ -805,14 +796,12 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     constexpr int kWpb2 = kAssignWpb<T, F>;
     constexpr int kThreads = kWpb2 * 64;
     static_assert(kThreads >= kPeakThreads, "the peak prologue takes two histogram slots per thread");
-    static_assert(kAssignLds(kWpb2) <= 160 * 1024, "LDS of one compute unit");
+    static_assert(kAssignLds<F>(kWpb2) <= 160 * 1024, "LDS of one compute unit");
     static_assert(kMfmaBins * kMfmaBins * 8 <= 2 * kMfmaBins * kKeyStride * 4, "the summed histogram fits in wave 0's arrays");
     // All LDS is static, so that table addresses are compile-time constants.
-    __shared__ __align__(16) unsigned char smem[kAssignLds(kWpb2)];
+    __shared__ __align__(16) unsigned char smem[kAssignLds<F>(kWpb2)];
     uint32_t *s_pop = reinterpret_cast<uint32_t *>(smem);                            // palette operands
-    uint32_t *s_cb = s_pop + kPopBytes / 4;                                          // [2][32] |P|^2 by bin
-    uint32_t *s_cbs = s_cb + 2 * kMfmaBins;                                           // [2][32] by slot
-    u32x4 *s_bo = reinterpret_cast<u32x4 *>(s_cbs + 2 * kMfmaBins);                // [kMaxBatchLds]
+    u32x4 *s_bo = reinterpret_cast<u32x4 *>(s_pop + kPopBytes<F> / 4);              // [kMaxBatchLds]
     uint32_t *s_bh = reinterpret_cast<uint32_t *>(s_bo + kMaxBatchLds);             // [kMaxBatchLds]
     uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bh + kMaxBatchLds);           // [32 * 32]
     int32_t *s_cnt = reinterpret_cast<int32_t *>(s_rank + kMfmaBins * kMfmaBins);   // [1024]
@@ -835,11 +824,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     uint32_t *ky = kx + kMfmaBins * kKeyStride;
     SliceLoad sl;
     if (list) slice_load(counts, nslices, sl);
-    for (int i = tid; i < kPopBytes / 16; i += kThreads) reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block(tb.pop, i, 0, 0);
-    if (tid < 2 * kMfmaBins) {
-        const int bin = tid & (kMfmaBins - 1);
-        s_cb[tid] = tid < kMfmaBins ? (bin < Bw ? tb.n2_x[bin] : 0u) : (bin < Bh ? tb.n2_y[bin] : 0u);
-    }
+    for (int i = tid; i < kPopBytes<F> / 16; i += kThreads)
+        reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, false>(tb.pop, i, 0, 0);
     for (int i = tid; i < kMfmaBins * kMfmaBins; i += kThreads) s_cnt[i] = 0;
     if (tid == 0) *s_next = 0;
     peaks_lds_sum(pld, s_h, pl);
@@ -858,7 +844,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     auto pixel = [&](int tt) { return cur_list.pixel(32 * tt + ln < n ? 32 * tt + ln : 32 * tt); };
     RawSlices<T, F> raw;
     int ip = t < tend ? pixel(t) : 0;                   // this lane's pixel in this tile
-    peaks_lds_find(Bw, Bh, cut, cap, s_h, pl, s_bo, s_bh, s_rank, s_cb, s_cbs, [&]() {
+    peaks_lds_find(Bw, Bh, cut, cap, s_h, pl, s_bo, s_bh, s_rank, [&]() {
         if (t < tend) raw.load(emb + (size_t)ip * dstride, yoff, g);
     });
     const int Kc = pl.Kc;
@@ -897,37 +883,32 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     // (the fast kernel reads them from LDS per tile: its search needs the
     // registers)
     const int slotbin[2] = {g * 32 + pl.colbin[ln], g * 32 + pl.rowbin[ln]};
-    i32x4 popr[2][kPopKinds];
-    if constexpr (!FAST) {
+    constexpr bool kPalRegs = !FAST && kSteps<F> == 1;
+    f16x8 popr[2][kAxisKinds<F>];
+    if constexpr (kPalRegs) {
 #pragma unroll
         for (int ax = 0; ax < 2; ax++)
 #pragma unroll
-            for (int k = 0; k < kPopKinds; k++) popr[ax][k] = palette_operand(s_pop, ax, k, slotbin[ax]);
+            for (int k = 0; k < kAxisKinds<F>; k++) popr[ax][k] = palette_operand<F>(s_pop, ax, k, slotbin[ax]);
     }
 
     // Distances of one tile (pixel m = lane & 31; this lane's 16 slots
-    // acc_row(r, g) of each axis); `next` reuses the input registers once
-    // they are converted.  The accumulators of the Xl.lo products start at
-    // the slots' |P|^2; the pixel's |X|^2 completes S.  EXACT: the correctly
-    // rounded square root of fl32(S); otherwise the hardware square root,
-    // within one binary32 step of it (the fast search below).
+    // acc_row(r, g) of each axis), scaled by 2^-7 (the root of kScale);
+    // `next` reuses the input registers once they are converted.  EXACT: the
+    // correctly rounded square root of fl32(S); otherwise the hardware square
+    // root, within one binary32 step of it (the fast search below).
     auto distances = [&](auto exact, RawSlices<T, F> &raw, auto next) {
-        int n2x = 0, n2y = 0;
-        AxisOp<F> X, Y;
-        raw.convert(0, X, n2x);
-        raw.convert(1, Y, n2y);
-        after_convert(X, Y, n2x, n2y);
+        PixOps<T, F> X;
+        X.from(raw);
         next();
-        const uint32_t npx = (uint32_t)(n2x + __shfl_xor(n2x, 32));
-        const uint32_t npy = (uint32_t)(n2y + __shfl_xor(n2y, 32));
 #pragma unroll
         for (int ax = 0; ax < 2; ax++) {
-            i32x16 hh, mid, ll;
-            i32x4 pop[kPopKinds];
+            f16x8 pop[kAxisKinds<F>];
 #pragma unroll
-            for (int k = 0; k < kPopKinds; k++) pop[k] = FAST ? palette_operand(s_pop, ax, k, slotbin[ax]) : popr[ax][k];
-            axis_products<F, false>(ax ? Y : X, pop, row_init(s_cbs + ax * kMfmaBins, g), hh, mid, ll);
-            const uint32_t np = ax ? npy : npx;
+            for (int k = 0; k < kAxisKinds<F>; k++)
+                pop[k] = kPalRegs ? popr[ax][k] : palette_operand<F>(s_pop, ax, k, slotbin[ax]);
+            f32x16 A, R;
+            axis_products<T, F, false>(X.ax[ax], X.e, pop, A, R);
             uint32_t *dst = (ax ? ky : kx) + 4 * g * kKeyStride + ln;
 #pragma unroll
             for (int r4 = 0; r4 < 4; r4++) {
@@ -935,7 +916,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
                     const int r = 4 * r4 + i;
-                    const float x = (float)assemble(hh[r], mid[r], ll[r], np);
+                    const float x = assemble(A[r], R[r]);
                     const float d = decltype(exact)::value ? sqrt_cr(x) : __builtin_amdgcn_sqrtf(x);
                     dst[kKeyStride * (8 * r4 + i)] = __float_as_uint(d);
                 }
@@ -949,8 +930,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     // computation and each read serve four pixels.  Per batch and pixel the
     // smallest of the 4 x distances plus the row's y distance, summed exactly
     // in binary64, has at least 12 zero bits at the bottom of its mantissa
-    // (both distances are 0 or binary32 values of at least 1, so the sum is a
-    // multiple of 2^-23 below 2^17), which take the batch index (< 128).  The
+    // (both distances are 0 or binary32 values of at least 2^-7, so the sum is
+    // a multiple of 2^-30 below 2^10), which take the batch index (< 128).  The
     // eight lanes of a pixel quad then combine their minima through LDS; lane
     // m takes pixel m's result, finds the first column of the winning batch
     // with the batch's smallest x distance, and (lanes of half 0, valid
@@ -1009,11 +990,11 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const uint32_t col = (w0 == wm ? ow.x : w1 == wm ? ow.y : w2 == wm ? ow.z : ow.w) >> 7;   // column slot
         const uint32_t row = s_bh[bi] >> 7;                                                      // row slot
         if (g == 0 && ln < nvalid) {
-            if (D < tau4096) {      // Eq8
+            if (D < tau32) {      // Eq8
                 const int a = pl.colbin[col], b = pl.rowbin[row];
                 const int k = s_rank[b * kMfmaBins + a] & (kMfmaBins * kMfmaBins - 1);
                 labels[pix] = k + 1;
-                if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-12));
+                if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-5));
                 atomicAdd(s_cnt + k, 1);
             } else {
                 labels[pix] = 0;
@@ -1038,7 +1019,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     // If the second smallest sum exceeds the smallest s_w by kFastGap steps
     // (each more than 2^-24 s_w), so by more than 2g / (1 - g) s_w, every
     // other batch's D exceeds the winning batch's (a sum of 0 is exact: any
-    // other distance sum is at least 1).
+    // other distance sum is at least 2^-7).
     // Within the winning batch (one row, exact distances of one y), a column
     // whose r~ is at least 3 steps above the batch's smallest r~ is strictly
     // farther.  When both hold the winner is the unique minimiser of the

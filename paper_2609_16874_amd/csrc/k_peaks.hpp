@@ -179,7 +179,7 @@ __device__ __forceinline__ bool is_peak32(const unsigned long long *s_h, int a, 
 // caller's, peaks_lds_find compacts the candidates in ascending bin order
 // (pl.pk) and writes K and min(K, cap), the bin -> candidate-index table
 // s_rank [32 * 32], the column and row slots (pl.ncol, pl.nrow, pl.colbin,
-// pl.rowbin, and the bin constants by slot s_cbs) and the candidate batches
+// pl.rowbin) and the candidate batches
 // s_bo / s_bh in slot offsets (pl.nbat of them, a multiple of kBatchPad).  `mid` runs between its first and second barrier
 // (the caller's independent work, e.g. loads whose latency the extraction
 // hides).
@@ -201,7 +201,7 @@ __device__ __forceinline__ void peaks_lds_sum(const PeakLoad &ld, unsigned long 
 template <typename Mid>
 __device__ __forceinline__ void peaks_lds_find(int Bw, int Bh, long long cut, int cap, const unsigned long long *s_h,
                                                PeakLds &pl, u32x4_pk *s_bo, uint32_t *s_bh, uint16_t *s_rank,
-                                               const uint32_t *s_cb, uint32_t *s_cbs, Mid mid)
+                                               Mid mid)
 {
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     constexpr int kWaves = kPeakThreads / 64;
@@ -245,9 +245,8 @@ __device__ __forceinline__ void peaks_lds_find(int Bw, int Bh, long long cut, in
     __syncthreads();
     // Slots: the candidate columns and rows, each numbered in ascending
     // order; the assignment computes distances for slots only, and its
-    // arrays, batches and bin constants are indexed by slot.  Lane j of the
-    // first wave numbers column j and row j and scatters them (and their
-    // bin constants, s_cb [2][32] by bin -> s_cbs [2][32] by slot).
+    // arrays and batches are indexed by slot.  Lane j of the first wave
+    // numbers column j and row j and scatters them.
     // Batches: lane b builds row b's (strict maxima are never horizontally
     // adjacent: <= 16 per row, <= 4 batches), as slot byte offsets.
     if (tid < 64) {
@@ -263,12 +262,8 @@ __device__ __forceinline__ void peaks_lds_find(int Bw, int Bh, long long cut, in
         if (b < kLdsPeakBins && ((cm >> b) & 1u)) {
             const int cs = __popc(cm & ((1u << b) - 1u));
             pl.colbin[cs] = (uint8_t)b;
-            s_cbs[cs] = s_cb[b];
         }
-        if (m) {
-            pl.rowbin[rslot] = (uint8_t)b;
-            s_cbs[kLdsPeakBins + rslot] = s_cb[kLdsPeakBins + b];
-        }
+        if (m) pl.rowbin[rslot] = (uint8_t)b;
         const int nbt = (__popc(m) + 3) >> 2;
         const int incl = wave_incl_sum(nbt);      // the whole first wave is active here
         const int start = incl - nbt, total = __builtin_amdgcn_readlane(incl, 31);

@@ -144,7 +144,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels);
         auto assign_kernel = fast ? k_assign_mfma<T, F, true> : k_assign_mfma<T, F, false>;
         if (!launch(2, assign_kernel, dim3(grid2), dim3(wpb2 * 64), 0, e, dstride, yoff, (const int32_t *)list,
-                    (const int32_t *)sc.counts, nslices, slice_px, npix, fa.tau4096, h->tb,
+                    (const int32_t *)sc.counts, nslices, slice_px, npix, fa.tau4096 * 0x1p-7, h->tb,
                     (const unsigned long long *)hcur, sc.hlast, Bw, Bh, cut, h->cap, cents, num, labels, score,
                     (int32_t)(h->search_mode == 1)))
             return CPE_ERR_HIP;
