@@ -43,7 +43,7 @@ struct Tables {
                               //   lane l (bin 32 block + (l & 31), K slots 8 (l >> 5) .. + 7); kinds:
                               //   norms of A, norms of R for S, for S + 1, then hi and lo of channels
                               //   0 .. 15 and of 16 .. 31; see k_mfma.hpp
-    const uint32_t *wt_pk;    // [kWKeys] weight as two fp16 limbs (q & 255) | (q >> 8) << 16,
+    const uint16_t *wt_pk;    // [kWKeys] weight q = lo - 256 nh as int8 limbs lo | nh << 8 (lo >= -128, nh <= 0),
                               //          at LDS position ((e + 17) & 31) * 256 + t
 };
 

@@ -89,14 +89,6 @@ double centre_distance(int key, int m)
     return std::sqrt(std::ldexp(1.0 + ((double)t + 0.5) / (double)(1 << m), e) - 1.0) / 4096.0;
 }
 
-uint16_t f16_bits(int v)   // exact for the small integers used here (|v| <= 2048)
-{
-    const _Float16 hv = (_Float16)(float)v;
-    uint16_t b;
-    std::memcpy(&b, &hv, 2);
-    return b;
-}
-
 // ---------------------------------------------------------------------------
 // Per-frame scratch of cpe_decode_noalloc: a static device array, one copy
 // per device, for frames of up to kStaticMaxPixels pixels and any bin grid.
@@ -260,11 +252,11 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     for (int k = 0; k < kWKeys; k++) h->wt[k] = (uint16_t)std::rint(32768.0 * std::exp(-centre_distance(k, kWMant)));
     // LDS order of the matrix-core kernels: bucket (e, t) at ((e + 17) & 31) << m | t,
     // so that (bits >> (23 - m)) & (2^(m+5) - 1) of 2^-14 fl32(S + 1) indexes it directly
-    std::vector<uint32_t> wt_pk(kWKeys);
+    std::vector<uint16_t> wt_pk(kWKeys);
     for (int k = 0; k < kWKeys; k++) {
         const int e = k >> kWMant, t = k & ((1 << kWMant) - 1);
-        const int q = h->wt[k];
-        wt_pk[(((e + 17) & 31) << kWMant) | t] = (uint32_t)f16_bits(q & 255) | ((uint32_t)f16_bits(q >> 8) << 16);
+        const int q = h->wt[k], lo = ((q + 128) & 255) - 128, nh = (lo - q) / 256;
+        wt_pk[(((e + 17) & 31) << kWMant) | t] = (uint16_t)((lo & 255) | (nh & 255) << 8);
     }
 
     auto pack = [&](int n, const std::vector<int16_t> &pal, std::vector<int32_t> &pk, std::vector<uint32_t> &n2) {
@@ -348,7 +340,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     const size_t o_wt = carve(kWKeys * 2);
     const size_t o_cx = carve(cx.size() * 4), o_cy = carve(cy.size() * 4);
     const size_t o_pop = carve(pop.size() * 2);
-    const size_t o_wpk = carve(wt_pk.size() * 4);
+    const size_t o_wpk = carve(wt_pk.size() * 2);
     const size_t o_hrep = carve(2 * (size_t)kReplicas * nb * 8);
     const size_t o_hlast = carve((size_t)nb * 8);
     const size_t o_peaks = carve((size_t)centroid_capacity * 4);
@@ -369,7 +361,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
               up(o_wt, h->wt.data(), kWKeys * 2) &&
               up(o_cx, cx.data(), cx.size() * 4) && up(o_cy, cy.data(), cy.size() * 4) &&
               up(o_pop, pop.data(), pop.size() * 2) &&
-              up(o_wpk, wt_pk.data(), wt_pk.size() * 4) &&
+              up(o_wpk, wt_pk.data(), wt_pk.size() * 2) &&
               hipMemset(d + o_hrep, 0, 2 * (size_t)kReplicas * nb * 8) == hipSuccess &&
               hipMemset(d + o_hlast, 0, (size_t)nb * 8) == hipSuccess &&
               hipMemset(d + o_kinfo, 0, 16) == hipSuccess && hipMemset(d + o_count, 0, (size_t)kMaxSlices * 4) == hipSuccess &&
@@ -387,7 +379,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     h->tb.cx = reinterpret_cast<const float *>(d + o_cx);
     h->tb.cy = reinterpret_cast<const float *>(d + o_cy);
     h->tb.pop = reinterpret_cast<const uint32_t *>(d + o_pop);
-    h->tb.wt_pk = reinterpret_cast<const uint32_t *>(d + o_wpk);
+    h->tb.wt_pk = reinterpret_cast<const uint16_t *>(d + o_wpk);
     h->sc.hrep = reinterpret_cast<unsigned long long *>(d + o_hrep);
     h->sc.set_stride = (size_t)kReplicas * nb;
     h->parity = 0;

@@ -39,10 +39,14 @@
 // as the MFMA rows, the distance result leaves in each lane one bin and 16
 // pixels -- exactly the operand layout of the vote contraction
 // H = Qx^T Qy over pixels, so the weights feed the second MFMA without any
-// data exchange between lanes.  A weight q <= 2^15 is split into fp16 limbs
-// q = 256 hi + lo; the four limb products accumulate in fp32 exactly as long
-// as at most 256 pixels are summed, after which they are added into a 64-bit
-// histogram in LDS.
+// data exchange between lanes.  A weight q <= 2^15 is split into int8 limbs
+// q = lo - 256 nh, -128 <= lo < 128 and nh = -hi in [-128, 0]; a tile's 32
+// pixels take one v_mfma_i32_32x32x32_i8 for each of the four limb products,
+// whose int32 sums hold for kFoldTiles tiles and are then added into a 64-bit
+// histogram in LDS.  (fp16 limbs, 16 pixels per instruction, took twice the
+// MFMAs, and their fp32 sums had to be folded every 8 tiles: 32.8 against
+// 31.5 us at 1024 x 2048, 86.7 against 78.3 us at 2160 x 3840 with 8
+// harmonics.)
 //
 // Pass 2, k_assign_mfma (assignment, Eq7, and label write-out).  Only the
 // candidate columns and rows are needed: they are numbered in ascending
@@ -100,6 +104,11 @@ struct AxisOp {
     static constexpr int NL = sizeof(T) == 2 ? 1 : 2;
     f16x8 a[NL][kSteps<F>];
 };
+
+__device__ __forceinline__ i32x16 mfma8(i32x4 a, i32x4 b, i32x16 c)
+{
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+}
 
 __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 {
@@ -358,13 +367,17 @@ __device__ __forceinline__ int take_tile(int *next, int lane, int first, int wav
 // (lanes = y bins, fixed x bin) into distinct banks.
 constexpr int kHStride = kMfmaBins + 1;
 
-// LDS bytes of k_vote_mfma: the packed weight table, the 64-bit histogram,
+// Tiles between two folds of a wave's limb sums: |nh lo| <= 2^14, so the
+// middle accumulator grows by at most 2^15 per pixel, 2^20 per tile.
+constexpr int kFoldTiles = 2047;
+
+// LDS bytes of k_vote_mfma: the weight table, the 64-bit histogram,
 // the palette operands, the slice prefix sums and counters; with the
 // compaction folded in (FUSED), the workgroup's own participating pixels.
 template <int F>
 constexpr size_t kVoteLds(bool fused)
 {
-    return (size_t)kWKeys * 4 + kMfmaBins * kHStride * 8 + kPopBytes<F> + (kMaxSlices + 1) * 4 + 16 + (fused ? (size_t)kFusedMaxSeg * 4 : 0);
+    return (size_t)kWKeys * 2 + kMfmaBins * kHStride * 8 + kPopBytes<F> + (kMaxSlices + 1) * 4 + 16 + (fused ? (size_t)kFusedMaxSeg * 4 : 0);
 }
 
 // Eight foreground values from pixel p0 on (p0 a multiple of 8), in two
@@ -471,7 +484,7 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     const int nbx = MULTI ? (Bw + kMfmaBins - 1) / kMfmaBins : 1, nby = MULTI ? (Bh + kMfmaBins - 1) / kMfmaBins : 1;
     // All LDS is static, so that table addresses are compile-time constants.
     __shared__ __align__(16) unsigned char smem[kVoteLds<F>(FUSED)];
-    uint32_t *s_wt = reinterpret_cast<uint32_t *>(smem);                              // [kWKeys] fp16 limb pairs
+    uint16_t *s_wt = reinterpret_cast<uint16_t *>(smem);                              // [kWKeys] int8 limb pairs
     unsigned long long *s_h = reinterpret_cast<unsigned long long *>(s_wt + kWKeys);  // [32][kHStride], b * kHStride + a
     uint32_t *s_pop = reinterpret_cast<uint32_t *>(s_h + kMfmaBins * kHStride);      // palette operands
     int *s_pref = reinterpret_cast<int *>(s_pop + kPopBytes<F> / 4);                  // [kMaxSlices + 1]
@@ -484,7 +497,7 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     SliceLoad sl;
     if (!FUSED && list) slice_load(counts, nslices, sl);
     {
-        constexpr int kThreads = kWpb * 64, kN = kWKeys / 4, kPer = (kN + kThreads - 1) / kThreads;
+        constexpr int kThreads = kWpb * 64, kN = kWKeys / 8, kPer = (kN + kThreads - 1) / kThreads;
         u32x4 w[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; k++) {
@@ -606,7 +619,7 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
         block_run(ntiles, blockIdx.x, gridDim.x, t0, tend);
     }
 
-    f32x16 acc2 = {}, acc1 = {}, acc0 = {};
+    i32x16 acc2 = {}, acc1 = {}, acc0 = {};       // sums of nh nh, nh lo + lo nh, lo lo
     int ntile = 0;
 
     // Add the limb sums into the workgroup's histogram (this wave owns every
@@ -614,18 +627,14 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     auto fold = [&]() {
 #pragma unroll
         for (int r = 0; r < 16; r++) {
-            const unsigned long long v = ((unsigned long long)(uint32_t)acc2[r] << 16) +
-                                         ((unsigned long long)(uint32_t)acc1[r] << 8) +
-                                         (unsigned long long)(uint32_t)acc0[r];
-            atomicAdd(&s_h[ln * kHStride + acc_row(r, g)], v);
-            acc2[r] = 0.0f;
-            acc1[r] = 0.0f;
-            acc0[r] = 0.0f;
+            const long long v = (long long)acc2[r] * 65536 - (long long)acc1[r] * 256 + acc0[r];
+            atomicAdd(&s_h[ln * kHStride + acc_row(r, g)], (unsigned long long)v);
+            acc2[r] = acc1[r] = acc0[r] = 0;
         }
     };
 
-    // Packed weight limbs of the 16 (pixel, bin) results of one axis: the
-    // binary32 bits of kScale (S + 1) give the bucket.
+    // Weight limbs (lo | nh << 8) of the 16 (pixel, bin) results of one axis:
+    // the binary32 bits of kScale (S + 1) give the bucket.
     auto weights = [&](const f32x16 &A, const f32x16 &R, uint32_t (&e)[16]) {
 #pragma unroll
         for (int r = 0; r < 16; r++) e[r] = s_wt[(__float_as_uint(assemble(A[r], R[r])) >> 15) & (kWKeys - 1)];
@@ -654,29 +663,24 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
             for (int r = 0; r < 16; r++)
                 if (acc_row(r, g) >= nvalid) ex[r] = 0u;
         }
-        // vote: K = the 16 pixels of this lane, in two MFMAs of 8
+        // vote: K = the 16 pixels of this lane, one byte each
+        u32x4 xl, xh, yl, yh;
 #pragma unroll
-        for (int t = 0; t < 2; t++) {
-            u32x4 xl, xh, yl, yh;
-#pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const int r = 8 * t + 2 * s;
-                xl[s] = __builtin_amdgcn_perm(ex[r + 1], ex[r], 0x05040100u);
-                xh[s] = __builtin_amdgcn_perm(ex[r + 1], ex[r], 0x07060302u);
-                yl[s] = __builtin_amdgcn_perm(ey[r + 1], ey[r], 0x05040100u);
-                yh[s] = __builtin_amdgcn_perm(ey[r + 1], ey[r], 0x07060302u);
-            }
-            const f16x8 XL = __builtin_bit_cast(f16x8, xl), XH = __builtin_bit_cast(f16x8, xh);
-            const f16x8 YL = __builtin_bit_cast(f16x8, yl), YH = __builtin_bit_cast(f16x8, yh);
-            acc2 = mfma16(XH, YH, acc2);
-            acc1 = mfma16(XH, YL, acc1);
-            acc1 = mfma16(XL, YH, acc1);
-            acc0 = mfma16(XL, YL, acc0);
+        for (int s = 0; s < 4; s++) {
+            const int r = 4 * s;
+            const uint32_t x01 = ex[r] | ex[r + 1] << 16, x23 = ex[r + 2] | ex[r + 3] << 16;
+            const uint32_t y01 = ey[r] | ey[r + 1] << 16, y23 = ey[r + 2] | ey[r + 3] << 16;
+            xl[s] = __builtin_amdgcn_perm(x23, x01, 0x06040200u);
+            xh[s] = __builtin_amdgcn_perm(x23, x01, 0x07050301u);
+            yl[s] = __builtin_amdgcn_perm(y23, y01, 0x06040200u);
+            yh[s] = __builtin_amdgcn_perm(y23, y01, 0x07050301u);
         }
-        if (++ntile == 8) {        // 256 pixels: fold before an fp32 sum could exceed 2^24
-            fold();
-            ntile = 0;
-        }
+        const i32x4 XL = __builtin_bit_cast(i32x4, xl), XH = __builtin_bit_cast(i32x4, xh);
+        const i32x4 YL = __builtin_bit_cast(i32x4, yl), YH = __builtin_bit_cast(i32x4, yh);
+        acc2 = mfma8(XH, YH, acc2);
+        acc1 = mfma8(XH, YL, acc1);
+        acc0 = mfma8(XL, YL, acc0);
+        acc1 = mfma8(XL, YH, acc1);
     };
 
     for (int blk = 0; blk < nbx * nby; blk++) {
@@ -720,9 +724,11 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
             });
             t = tn;
             tn = tnn;
+            if (++ntile == kFoldTiles || t >= tend) {
+                fold();
+                ntile = 0;
+            }
         }
-        fold();
-        ntile = 0;
 
         // one global atomic per bin of the block
         __syncthreads();
