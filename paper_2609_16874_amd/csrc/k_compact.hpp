@@ -145,42 +145,40 @@ __global__ __launch_bounds__(256) __attribute__((unused)) void k_clear_u64(unsig
 }  // namespace
 
 // Exclusive prefix sums s_pref[0 .. nslices] of the slice counts (LDS),
-// s_pref[nslices] = |S|, by the first wave: slice_load issues the loads
-// (lane l holds slices 4 l .. 4 l + 3), slice_scan writes the sums.  Split
-// so that the caller can issue its other loads in between; the caller's
-// barrier publishes s_pref.
+// s_pref[nslices] = |S|.  Every wave computes and writes all of them (the same
+// values), so that it can go on to its first list entries without a barrier:
+// its own LDS accesses are in order.  slice_load issues the loads (lane l
+// holds slices 4 l .. 4 l + 3), slice_scan writes the sums and returns |S|.
 struct SliceLoad {
     int c[kMaxSlices / 64];
 };
 __device__ __forceinline__ void slice_load(const int32_t *__restrict__ counts, int nslices, SliceLoad &sl)
 {
-    const int tid = threadIdx.x;
-    if (tid < 64) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-        for (int k = 0; k < kMaxSlices / 64; k++) {
-            const int s = 4 * tid + k;
-            sl.c[k] = s < nslices ? counts[s] : 0;
-        }
+    for (int k = 0; k < kMaxSlices / 64; k++) {
+        const int s = 4 * lane + k;
+        sl.c[k] = s < nslices ? counts[s] : 0;
     }
 }
-__device__ __forceinline__ void slice_scan(const SliceLoad &sl, int nslices, int *s_pref)
+__device__ __forceinline__ int slice_scan(const SliceLoad &sl, int nslices, int *s_pref)
 {
-    const int tid = threadIdx.x;
-    if (tid < 64) {
-        int sum = 0;
+    const int lane = threadIdx.x & 63;
+    int sum = 0;
 #pragma unroll
-        for (int k = 0; k < kMaxSlices / 64; k++) sum += sl.c[k];
-        const int incl = wave_incl_sum(sum);
-        int run = incl - sum;
+    for (int k = 0; k < kMaxSlices / 64; k++) sum += sl.c[k];
+    const int incl = wave_incl_sum(sum);
+    int run = incl - sum;
 #pragma unroll
-        for (int k = 0; k < kMaxSlices / 64; k++) {
-            const int s = 4 * tid + k;
-            if (s <= nslices) s_pref[s] = run;
-            run += sl.c[k];
-        }
-        // the lanes' slices end at kMaxSlices - 1: the total for nslices == kMaxSlices
-        if (tid == 63) s_pref[nslices] = incl;
+    for (int k = 0; k < kMaxSlices / 64; k++) {
+        const int s = 4 * lane + k;
+        if (s <= nslices) s_pref[s] = run;
+        run += sl.c[k];
     }
+    // the lanes' slices end at kMaxSlices - 1: the total for nslices == kMaxSlices
+    if (lane == 63) s_pref[nslices] = incl;
+    __builtin_amdgcn_wave_barrier();
+    return __builtin_amdgcn_readlane(incl, 63);
 }
 
 // The concatenated slices seen by one lane whose positions never decrease:

@@ -495,6 +495,7 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane >> 5, ln = lane & 31;
     SliceLoad sl;
+    int nlist = npix;
     if (!FUSED && list) slice_load(counts, nslices, sl);
     {
         constexpr int kThreads = kWpb * 64, kN = kWKeys / 8, kPer = (kN + kThreads - 1) / kThreads;
@@ -605,11 +606,11 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
         for (int i = tid; i < kPopBytes<F> / 16; i += kThreads)
             reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, true>(tb.pop, i, 0, 0);
         if (tid == 0) *s_next = 0;
-        if (!FUSED && list) slice_scan(sl, nslices, s_pref);
+        if (!FUSED && list) nlist = slice_scan(sl, nslices, s_pref);
     }
     __syncthreads();
     // the workgroup's run of tiles: a share of the list, or (FUSED) its own pixels
-    const int n = FUSED ? *s_cnt : list ? s_pref[nslices] : npix, ntiles = (n + 31) >> 5;
+    const int n = FUSED ? *s_cnt : nlist, ntiles = (n + 31) >> 5;
     int t0, tend;
     if constexpr (FUSED) {
         t0 = 0;
@@ -757,18 +758,17 @@ constexpr int kAssignWaves = (F <= 9 || (sizeof(T) == 2 && F == 16)) ? 4 : 3;
 template <typename T, int F>
 constexpr int kAssignWpb = 4 * kAssignWaves<T, F>;
 
-// LDS bytes of k_assign_mfma: palette operands, |P|^2 by bin and by slot,
-// candidate batches, bin -> centroid table, counts, per wave x and y
-// distances [32 slots][kKeyStride] (u32), then the peak-extraction state
-// (the searches merge their lanes' partial results in a wave's y array once
-// it is no longer read).  The summed vote histogram (32 x 32 slots, 8 KB) of the prologue
-// shares its bytes with the first waves' distance arrays, which are written
-// only after it is no longer read.
+// LDS bytes of k_assign_mfma: palette operands, candidate batches, counts,
+// per wave x and y distances [32 slots][kKeyStride] (u32), then the
+// peak-extraction state (the searches merge their lanes' partial results in a
+// wave's y array once it is no longer read).  The summed vote histogram of
+// the prologue (kPadHist counts, 9 KB) shares its bytes with the first waves'
+// distance arrays, which are written only after it is no longer read.
 template <int F>
 constexpr size_t kAssignLdsCore(int wpb)
 {
-    return (size_t)kPopBytes<F> + (size_t)kMaxBatchLds * 20 + kMfmaBins * kMfmaBins * 2 +
-           kMfmaBins * kMfmaBins * 4 + (size_t)wpb * 2 * kMfmaBins * kKeyStride * 4 + sizeof(PeakLds) +
+    return (size_t)kPopBytes<F> + (size_t)kMaxBatchLds * 24 + kMfmaBins * kMfmaBins * 4 +
+           (size_t)wpb * 2 * kMfmaBins * kKeyStride * 4 + sizeof(PeakLds) +
            (kMaxSlices + 1) * 4 + 16;
 }
 template <int F>
@@ -780,7 +780,14 @@ constexpr size_t kAssignLds(int wpb)
 // Every workgroup first sums the vote histograms `hcur` of the vote launch
 // and extracts the peaks in LDS (identical in every workgroup); workgroup 0
 // writes the centroid records (all fields but the pixel count), K and the
-// summed histogram `hlast`.
+// summed histogram `hlast`.  This prologue is a chain of memory round trips
+// and of code fetched cold, paid by every frame: with every wave scanning the
+// slice counts for itself (its first list entries load before the first
+// barrier), a bordered histogram instead of range checks and the candidates'
+// indices kept with the batches (instead of a bin -> index table, two
+// dependent LDS reads per labelled pixel) it takes 5.0 us at 640 x 640; the
+// launch went from 9.8 to 7.9 us at 64 x 64 and from 18.7 to 17.1 us at 640 x
+// 640, 16 harmonics, fp16.
 //
 // Then, per tile of 32 pixels, the distances of both axes for the candidate
 // slots (palette entries of the slots' bins as the MFMA rows, so that each
@@ -801,46 +808,49 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
 {
     constexpr int kWpb2 = kAssignWpb<T, F>;
     constexpr int kThreads = kWpb2 * 64;
-    static_assert(kThreads >= kPeakThreads, "the peak prologue takes two histogram slots per thread");
     static_assert(kAssignLds<F>(kWpb2) <= 160 * 1024, "LDS of one compute unit");
-    static_assert(kMfmaBins * kMfmaBins * 8 <= 2 * kMfmaBins * kKeyStride * 4, "the summed histogram fits in wave 0's arrays");
+    static_assert(kPadHist * 8 <= kWpb2 * 2 * kMfmaBins * kKeyStride * 4, "the summed histogram fits in the waves' arrays");
     // All LDS is static, so that table addresses are compile-time constants.
     __shared__ __align__(16) unsigned char smem[kAssignLds<F>(kWpb2)];
     uint32_t *s_pop = reinterpret_cast<uint32_t *>(smem);                            // palette operands
     u32x4 *s_bo = reinterpret_cast<u32x4 *>(s_pop + kPopBytes<F> / 4);              // [kMaxBatchLds]
     uint32_t *s_bh = reinterpret_cast<uint32_t *>(s_bo + kMaxBatchLds);             // [kMaxBatchLds]
-    uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bh + kMaxBatchLds);           // [32 * 32]
-    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_rank + kMfmaBins * kMfmaBins);   // [1024]
+    uint32_t *s_bk = s_bh + kMaxBatchLds;                                            // [kMaxBatchLds]
+    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_bk + kMaxBatchLds);              // [1024]
     uint32_t *s_keys = reinterpret_cast<uint32_t *>(s_cnt + kMfmaBins * kMfmaBins); // [kWpb2][2][32][kKeyStride]
     PeakLds &pl = *reinterpret_cast<PeakLds *>(s_keys + kWpb2 * 2 * kMfmaBins * kKeyStride);
     int *s_pref = reinterpret_cast<int *>(&pl + 1);                                  // [kMaxSlices + 1]
     int *s_next = s_pref + kMaxSlices + 1;                                            // next tile of the run
-    unsigned long long *s_h = reinterpret_cast<unsigned long long *>(s_keys);              // [32 * 32] summed votes
+    long long *s_h = reinterpret_cast<long long *>(s_keys);                          // [kPadHist] summed votes
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane >> 5, ln = lane & 31;
-    const int nb = Bw * Bh;
 
-    PeakLoad pld;                                   // issued before the table staging
-    peaks_lds_load(hcur, Bw, Bh, pld);
+    // Loads, in the order in which they are waited for: the slice counts (on
+    // which the first tile's list entries and then its rows depend), the
+    // vote counts, the palette operands.
+    SliceLoad sl;
+    if (list) slice_load(counts, nslices, sl);
+    PeakBins<kWpb2> pb;
+    pb.load(hcur, Bw, Bh);
+    constexpr int kPopPer = (kPopBytes<F> / 16 + kThreads - 1) / kThreads;
+    u32x4 pop[kPopPer];
+#pragma unroll
+    for (int k = 0; k < kPopPer; k++) {
+        const int i = k * kThreads + tid;
+        pop[k] = pop_block<F, false>(tb.pop, i < kPopBytes<F> / 16 ? i : 0, 0, 0);
+    }
     // This wave's search arrays, [slot][kKeyStride] per axis: x key of column
     // slot j, pixel m at kx[j * kKeyStride + m], y distance of row slot j at
     // ky[...].
     uint32_t *kx = s_keys + wv * 2 * kMfmaBins * kKeyStride;
     uint32_t *ky = kx + kMfmaBins * kKeyStride;
-    SliceLoad sl;
-    if (list) slice_load(counts, nslices, sl);
-    for (int i = tid; i < kPopBytes<F> / 16; i += kThreads)
-        reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, false>(tb.pop, i, 0, 0);
     for (int i = tid; i < kMfmaBins * kMfmaBins; i += kThreads) s_cnt[i] = 0;
     if (tid == 0) *s_next = 0;
-    peaks_lds_sum(pld, s_h, pl);
-    if (list) slice_scan(sl, nslices, s_pref);
-    __syncthreads();
 
     // the workgroup's run of tiles of 32 list entries; the first tile's list
     // entries and rows are loaded while the peaks are extracted
-    const int n = list ? s_pref[nslices] : npix, ntiles = (n + 31) >> 5;
+    const int n = list ? slice_scan(sl, nslices, s_pref) : npix, ntiles = (n + 31) >> 5;
     int t0, tend;
     block_run(ntiles, blockIdx.x, gridDim.x, t0, tend);
     int t = t0 + wv;
@@ -850,25 +860,38 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     auto pixel = [&](int tt) { return cur_list.pixel(32 * tt + ln < n ? 32 * tt + ln : 32 * tt); };
     RawSlices<T, F> raw;
     int ip = t < tend ? pixel(t) : 0;                   // this lane's pixel in this tile
-    peaks_lds_find(Bw, Bh, cut, cap, s_h, pl, s_bo, s_bh, s_rank, [&]() {
+    pb.store(s_h, Bw, Bh);
+#pragma unroll
+    for (int k = 0; k < kPopPer; k++) {
+        const int i = k * kThreads + tid;
+        if (i < kPopBytes<F> / 16) reinterpret_cast<u32x4 *>(s_pop)[i] = pop[k];
+    }
+    __syncthreads();
+    peaks_lds_find<kWpb2>(pb, cut, cap, s_h, pl, s_bo, s_bh, s_bk, [&]() {
         if (t < tend) raw.load(emb + (size_t)ip * dstride, yoff, g);
     });
+    // s_h is read; its bytes become distance arrays
     const int Kc = pl.Kc;
     if (blockIdx.x == 0) {
-        for (int k = tid; k < Kc; k += kThreads) {
-            const int i = pl.pk[k], a = i & 31, b = i >> 5;
-            cpe_centroid *c = cents + k;    // npix was reset by the vote launch and is counted below
-            c->bin_x = a;
-            c->bin_y = b;
-            c->x = tb.cx[a];
-            c->y = tb.cy[b];
-            c->score = (double)s_h[i] * 0x1p-30;
-            c->reserved = 0;
+#pragma unroll
+        for (int u = 0; u < PeakBins<kWpb2>::N; u++) {
+            int a, b;
+            if (!PeakBins<kWpb2>::pair(u, a, b) || a >= Bw || b >= Bh) continue;
+            const uint32_t m = pl.rowmask[b];
+            hlast[b * Bw + a] = (unsigned long long)pb.sum[u];
+            if ((m >> a) & 1u) {
+                // npix was reset by the vote launch and is counted below
+                cpe_centroid *c = cents + pl.rowfirst[b] + __popc(m & ((1u << a) - 1u));
+                c->bin_x = a;
+                c->bin_y = b;
+                c->x = tb.cx[a];
+                c->y = tb.cy[b];
+                c->score = (double)pb.sum[u] * 0x1p-30;
+                c->reserved = 0;
+            }
         }
-        for (int i = tid; i < nb; i += kThreads) hlast[i] = s_h[(i / Bw) * 32 + i % Bw];
         if (tid == 0) *num = pl.K;
     }
-    __syncthreads();        // s_h is read; its bytes become distance arrays
 
     if (Kc == 0) {              // no centroid: every participating pixel is unlabelled
         ListCursor c0;
@@ -993,12 +1016,10 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + ow.z);
         const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + ow.w);
         const uint32_t wm = min(min(w0, w1), min(w2, w3));
-        const uint32_t col = (w0 == wm ? ow.x : w1 == wm ? ow.y : w2 == wm ? ow.z : ow.w) >> 7;   // column slot
-        const uint32_t row = s_bh[bi] >> 7;                                                      // row slot
+        // the batch's first column at its minimum
+        const int k = (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
         if (g == 0 && ln < nvalid) {
             if (D < tau32) {      // Eq8
-                const int a = pl.colbin[col], b = pl.rowbin[row];
-                const int k = s_rank[b * kMfmaBins + a] & (kMfmaBins * kMfmaBins - 1);
                 labels[pix] = k + 1;
                 if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-5));
                 atomicAdd(s_cnt + k, 1);
@@ -1120,8 +1141,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const bool valid = g == 0 && ln < nvalid;
         if (force_exact || __ballot(amb && valid)) return false;
         if (valid) {
-            const int a = pl.colbin[oc >> 7], bb_ = pl.rowbin[s_bh[bi] >> 7];
-            const int k = s_rank[bb_ * kMfmaBins + a] & (kMfmaBins * kMfmaBins - 1);
+            const int k = (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
             labels[pix] = k + 1;
             atomicAdd(s_cnt + k, 1);
         }
@@ -1160,10 +1180,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + o.z);
         const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + o.w);
         const uint32_t wm = min(min(w0, w1), min(w2, w3));
-        const uint32_t col = (w0 == wm ? o.x : w1 == wm ? o.y : w2 == wm ? o.z : o.w) >> 7;
         if (g == 0 && ln < nvalid) {
-            const int a = pl.colbin[col], b = pl.rowbin[s_bh[bi] >> 7];
-            const int k = s_rank[b * kMfmaBins + a] & (kMfmaBins * kMfmaBins - 1);
+            const int k = (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
             labels[pix] = k + 1;
             atomicAdd(s_cnt + k, 1);
         }

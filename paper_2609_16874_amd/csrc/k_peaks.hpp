@@ -7,8 +7,8 @@
 //
 //   peaks_lds     grids up to 32 x 32: run by every workgroup of the
 //                 matrix-core assignment kernel in its prologue, entirely in
-//                 LDS.  Besides the compact list it builds the bin -> index
-//                 table and the candidate batches of the assignment search.
+//                 LDS, as candidate masks of the rows and the candidate
+//                 batches of the assignment search.
 //   peak_extract  any grid: the stand-alone kernel k_peaks between the
 //                 generic vote and assignment kernels; it writes the records,
 //                 K, the compact list and the summed histogram to memory.
@@ -16,10 +16,10 @@
 // Candidate batches.  The first min(K, cap) candidates are grouped by row b
 // into batches of 4 columns (a row's last batch repeats its last column,
 // which leaves a minimum unchanged).  Batch i is bo[i] = the byte offsets
-// a * 128 of its 4 columns in the assignment kernel's [bin][32 pixels] x-key
-// array, and bh[i] = 128 b, which is both the byte offset of row b in its
-// [bin][32 pixels] y-key array and the row's bits of the search key.  The
-// list is padded to a multiple of 8 batches with copies of its last one.
+// 128 j of its 4 column slots j in the assignment kernel's [slot][32 pixels]
+// x array, bh[i] the byte offset of its row's slot in the y array, and bk[i]
+// the index of its first candidate.  The list is padded to a multiple of 8
+// batches with copies of its last one.
 #pragma once
 
 #include "cpe_common.hpp"
@@ -112,161 +112,136 @@ __device__ __forceinline__ int compact_peaks(const unsigned long long *s_h, int 
 // ---------------------------------------------------------------------------
 // Grids up to 32 x 32: candidates in LDS, in the assignment kernel's prologue
 // ---------------------------------------------------------------------------
-// The histogram is held in a 32 x 32 slot layout, slot b * 32 + a, whose
-// order agrees with the bin order b * B_w + a.  The first kPeakThreads
-// threads of the block own two slots each: t and t + kPeakThreads.
+// A wave owns pairs of rows: pair p (rows 2 p and 2 p + 1) belongs to wave p
+// mod waves, lane l holding column l & 31 of row 2 p + (l >> 5), so that one
+// ballot is the candidate mask of both rows.
 constexpr int kLdsPeakBins = 32;
-constexpr int kPeakThreads = 512;
 constexpr int kMaxBatchLds = 128;   // <= 16 strict maxima per row of 32 -> <= 4 batches per row
 constexpr int kBatchPad = 8;        // the batch list is padded to a multiple of this
 constexpr int kKeyStride = 32;      // words per bin row of the assignment kernel's key arrays
+constexpr int kPadRow = kLdsPeakBins + 2;                  // the summed histogram in LDS: rows of 34 counts,
+constexpr int kPadHist = kPadRow * (kLdsPeakBins + 2);     //   a border of -1 around the 32 x 32 bins
 
 // LDS of peaks_lds (the summed histogram may alias any scratch the caller
 // does not need until the peaks are known).
 struct PeakLds {
-    int wave[2 * kPeakThreads / 64];  // per-wave counts of the two slot passes (slot-owning waves)
     uint32_t rowmask[kLdsPeakBins];   // bit a of row b: (a, b) is one of the first min(K, cap) candidates
-    uint32_t colmask;                 // bit a: column a holds one of them
+    int rowfirst[kLdsPeakBins];       // index of row b's first candidate
     int K, Kc, nbat;                  // nbat: batches, padded to a multiple of kBatchPad
     int nbat_real;                    // batches before the padding
     int ncol, nrow;                   // candidate columns and rows
     uint8_t colbin[kLdsPeakBins];     // column of column slot j (ascending; 0 past ncol)
     uint8_t rowbin[kLdsPeakBins];     // row of row slot j (ascending; 0 past nrow)
-    int pk[max_peaks(kLdsPeakBins, kLdsPeakBins)];   // candidate slots b * 32 + a, ascending
 };
 
-// The vote counts of this thread's two slots, summed over the kReplicas
-// histograms `hsrc` ([kReplicas][Bh][Bw], written by the previous launch).
-// Issued first, so that their latency overlaps the caller's table staging.
-struct PeakLoad {
-    unsigned long long v[2][kReplicas];
+// This thread's bins (one per row pair of its wave, WAVES waves): the vote
+// counts of the kReplicas histograms `hsrc` ([kReplicas][Bh][Bw], written by
+// the previous launch), and their sum.  The loads are issued first, so that
+// their latency overlaps the caller's table staging.
+template <int WAVES>
+struct PeakBins {
+    static constexpr int N = (kLdsPeakBins / 2 + WAVES - 1) / WAVES;
+    unsigned long long v[N][kReplicas];
+    long long sum[N];
+
+    __device__ __forceinline__ static bool pair(int u, int &a, int &b)
+    {
+        const int tid = threadIdx.x, p = (tid >> 6) + u * WAVES;
+        a = tid & 31;
+        b = 2 * p + ((tid >> 5) & 1);
+        return p < kLdsPeakBins / 2;          // wave-uniform
+    }
+    __device__ __forceinline__ void load(const unsigned long long *__restrict__ hsrc, int Bw, int Bh)
+    {
+#pragma unroll
+        for (int u = 0; u < N; u++) {
+            int a, b;
+            const bool in = pair(u, a, b) && a < Bw && b < Bh;
+#pragma unroll
+            for (int r = 0; r < kReplicas; r++) v[u][r] = in ? hsrc[(size_t)r * Bw * Bh + b * Bw + a] : 0ull;
+        }
+    }
+    // The sums into s_h [kPadHist], -1 in the border and past the grid.
+    __device__ __forceinline__ void store(long long *s_h, int Bw, int Bh)
+    {
+#pragma unroll
+        for (int u = 0; u < N; u++) {
+            int a, b;
+            if (!pair(u, a, b)) continue;
+            unsigned long long s = 0;
+#pragma unroll
+            for (int r = 0; r < kReplicas; r++) s += v[u][r];
+            sum[u] = a < Bw && b < Bh ? (long long)s : -1;
+            s_h[(b + 1) * kPadRow + a + 1] = sum[u];
+        }
+        const int i = threadIdx.x, c = i < 2 * kPadRow ? i % kPadRow : 0;
+        if (i < 2 * kPadRow)
+            s_h[(i < kPadRow ? 0 : (kPadRow - 1) * kPadRow) + c] = -1;
+        else if (i < 2 * kPadRow + 2 * kLdsPeakBins)
+            s_h[((i - 2 * kPadRow) / 2 + 1) * kPadRow + (i & 1) * (kPadRow - 1)] = -1;
+    }
 };
-__device__ __forceinline__ void peaks_lds_load(const unsigned long long *__restrict__ hsrc, int Bw, int Bh,
-                                               PeakLoad &ld)
-{
-    const int nb = Bw * Bh;
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const int slot = u * kPeakThreads + (int)threadIdx.x, a = slot & 31, b = slot >> 5;
-        const bool in = (int)threadIdx.x < kPeakThreads && a < Bw && b < Bh;
-#pragma unroll
-        for (int r = 0; r < kReplicas; r++) ld.v[u][r] = in ? hsrc[(size_t)r * nb + b * Bw + a] : 0ull;
-    }
-}
 
-// Strict 8-neighbour local maximum of slot (a, b) of s_h above `cut`;
-// out-of-range neighbours are ignored.
-__device__ __forceinline__ bool is_peak32(const unsigned long long *s_h, int a, int b, int Bw, int Bh, long long cut)
+// The extraction, called by every thread of the block after a barrier that
+// publishes s_h: the candidate masks of the rows, then the column and row
+// slots and the candidate batches s_bo / s_bh / s_bk (pl.nbat of them, a
+// multiple of kBatchPad; s_bk[i] = index of batch i's first candidate, so
+// column c of the batch is candidate s_bk[i] + c).  Everything follows from
+// the row masks: the candidates are in bin order, so a row's are consecutive.
+// `mid` runs after the first barrier (the caller's independent work, e.g.
+// loads whose latency the extraction hides).  A cold launch pays for the
+// instruction fetch of this code about as much as for its execution, hence
+// the border instead of range checks, and one bin per lane.
+template <int WAVES, typename Mid>
+__device__ __forceinline__ void peaks_lds_find(const PeakBins<WAVES> &pb, long long cut, int cap,
+                                               const long long *s_h, PeakLds &pl, u32x4_pk *s_bo, uint32_t *s_bh,
+                                               uint32_t *s_bk, Mid mid)
 {
-    const unsigned long long v = s_h[b * 32 + a];
-    bool f = a < Bw && b < Bh && (long long)v > cut;
+    const int tid = threadIdx.x, lane = tid & 63;
 #pragma unroll
-    for (int db = -1; db <= 1; db++)
+    for (int u = 0; u < PeakBins<WAVES>::N; u++) {
+        int a, b;
+        if (!PeakBins<WAVES>::pair(u, a, b)) continue;
+        const long long v = pb.sum[u], *q = s_h + b * kPadRow + a;      // the corner of its neighbourhood
+        bool f = v > cut;                                              // cut >= -1: false past the grid
 #pragma unroll
-        for (int da = -1; da <= 1; da++) {
-            if (!da && !db) continue;
-            const int nb_ = b + db, na = a + da;
-            const bool in = nb_ >= 0 && nb_ < Bh && na >= 0 && na < Bw;
-            const unsigned long long w = s_h[in ? nb_ * 32 + na : b * 32 + a];   // self when out of range
-            f = f && (!in || v > w);
+        for (int n = 0; n < 9; n++)
+            if (n != 4) f &= v > q[(n / 3) * kPadRow + n % 3];
+        const unsigned long long m = __ballot(f);
+        if (lane == 0) {
+            pl.rowmask[b] = (uint32_t)m;
+            pl.rowmask[b + 1] = (uint32_t)(m >> 32);
         }
-    return f;
-}
-
-// The extraction in two parts, called by every thread of a block of at
-// least kPeakThreads threads.  peaks_lds_sum stores the summed histogram
-// s_h (32 x 32 slots) from the loaded counts; after a barrier of the
-// caller's, peaks_lds_find compacts the candidates in ascending bin order
-// (pl.pk) and writes K and min(K, cap), the bin -> candidate-index table
-// s_rank [32 * 32], the column and row slots (pl.ncol, pl.nrow, pl.colbin,
-// pl.rowbin) and the candidate batches
-// s_bo / s_bh in slot offsets (pl.nbat of them, a multiple of kBatchPad).  `mid` runs between its first and second barrier
-// (the caller's independent work, e.g. loads whose latency the extraction
-// hides).
-__device__ __forceinline__ void peaks_lds_sum(const PeakLoad &ld, unsigned long long *s_h, PeakLds &pl)
-{
-    const int tid = threadIdx.x;
-    if (tid < kPeakThreads) {
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            unsigned long long sum = 0;
-#pragma unroll
-            for (int r = 0; r < kReplicas; r++) sum += ld.v[u][r];
-            s_h[u * kPeakThreads + tid] = sum;
-        }
-    }
-    if (tid < kLdsPeakBins) pl.rowmask[tid] = 0u;
-    if (tid == 0) pl.colmask = 0u;
-}
-template <typename Mid>
-__device__ __forceinline__ void peaks_lds_find(int Bw, int Bh, long long cut, int cap, const unsigned long long *s_h,
-                                               PeakLds &pl, u32x4_pk *s_bo, uint32_t *s_bh, uint16_t *s_rank,
-                                               Mid mid)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    constexpr int kWaves = kPeakThreads / 64;
-    const bool own = tid < kPeakThreads;            // wave-uniform
-    bool flag[2];
-    unsigned long long mask[2];
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const int slot = u * kPeakThreads + tid;
-        flag[u] = own && is_peak32(s_h, slot & 31, slot >> 5, Bw, Bh, cut);
-        mask[u] = __ballot(flag[u]);
-    }
-    if (own && lane == 0) {
-        pl.wave[wid] = __popcll(mask[0]);
-        pl.wave[kWaves + wid] = __popcll(mask[1]);
     }
     __syncthreads();
     mid();
-    int off0 = 0, off1 = 0, K = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; w++) {
-        const int n0 = pl.wave[w], n1 = pl.wave[kWaves + w];
-        off0 += w < wid ? n0 : 0;
-        off1 += n0 + (w < wid ? n1 : 0);
-        K += n0 + n1;
-    }
-    const int Kc = K < cap ? K : cap;
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-        if (flag[u]) {
-            const int slot = u * kPeakThreads + tid;
-            const int pos = (u ? off1 : off0) + lane_prefix(mask[u]);   // < max_peaks(32, 32)
-            pl.pk[pos] = slot;
-            if (pos < Kc) {
-                s_rank[slot] = (uint16_t)pos;
-                atomicOr(&pl.rowmask[slot >> 5], 1u << (slot & 31));
-                atomicOr(&pl.colmask, 1u << (slot & 31));
-            }
-        }
-    }
-    __syncthreads();
     // Slots: the candidate columns and rows, each numbered in ascending
     // order; the assignment computes distances for slots only, and its
-    // arrays and batches are indexed by slot.  Lane j of the first wave
-    // numbers column j and row j and scatters them.
-    // Batches: lane b builds row b's (strict maxima are never horizontally
-    // adjacent: <= 16 per row, <= 4 batches), as slot byte offsets.
+    // arrays and batches are indexed by slot.  Lane b of the first wave owns
+    // row b: it cuts the row's candidates off at `cap`, numbers column b and
+    // row b and builds the row's batches (strict maxima are never
+    // horizontally adjacent: <= 16 per row, <= 4 batches).
     if (tid < 64) {
         const int b = tid;
         uint32_t m = b < kLdsPeakBins ? pl.rowmask[b] : 0u;
-        const uint32_t cm = pl.colmask;
+        const int c = __popc(m), upto = wave_incl_sum(c), first = upto - c;    // the whole first wave is active
+        const int K = __builtin_amdgcn_readlane(upto, kLdsPeakBins - 1);
+        for (int over = min(upto - cap, c); over > 0; over--) m &= ~(0x80000000u >> __clz(m));
+        const uint32_t cm = wave_or32(m);
         const unsigned long long rows = __ballot(m != 0u);
         const int rslot = lane_prefix(rows);                         // slot of row b if it holds candidates
         if (b < kLdsPeakBins) {
+            pl.rowmask[b] = m;
+            pl.rowfirst[b] = first;
             pl.colbin[b] = 0;
             pl.rowbin[b] = 0;
         }
-        if (b < kLdsPeakBins && ((cm >> b) & 1u)) {
-            const int cs = __popc(cm & ((1u << b) - 1u));
-            pl.colbin[cs] = (uint8_t)b;
-        }
+        __builtin_amdgcn_wave_barrier();
+        if (b < kLdsPeakBins && ((cm >> b) & 1u)) pl.colbin[__popc(cm & ((1u << b) - 1u))] = (uint8_t)b;
         if (m) pl.rowbin[rslot] = (uint8_t)b;
         const int nbt = (__popc(m) + 3) >> 2;
-        const int incl = wave_incl_sum(nbt);      // the whole first wave is active here
-        const int start = incl - nbt, total = __builtin_amdgcn_readlane(incl, 31);
+        const int incl = wave_incl_sum(nbt);
+        const int start = incl - nbt, total = __builtin_amdgcn_readlane(incl, kLdsPeakBins - 1);
         const int padded = (total + kBatchPad - 1) & ~(kBatchPad - 1);
         const uint32_t hb = (uint32_t)rslot * (4u * kKeyStride);
         uint32_t last = 0;
@@ -283,6 +258,7 @@ __device__ __forceinline__ void peaks_lds_find(int Bw, int Bh, long long cut, in
             }
             s_bo[start + j] = o;
             s_bh[start + j] = hb;
+            s_bk[start + j] = (uint32_t)(first + 4 * j);
         }
         // pad the list with copies of the last batch (a repeated batch leaves
         // every minimum unchanged)
@@ -290,10 +266,11 @@ __device__ __forceinline__ void peaks_lds_find(int Bw, int Bh, long long cut, in
             for (int e = total; e < padded; e++) {
                 s_bo[e] = o;
                 s_bh[e] = hb;
+                s_bk[e] = (uint32_t)(first + 4 * (nbt - 1));
             }
         if (tid == 0) {
             pl.K = K;
-            pl.Kc = Kc;
+            pl.Kc = K < cap ? K : cap;
             pl.nbat = padded;
             pl.nbat_real = total;
             pl.ncol = __popc(cm);
