@@ -55,12 +55,11 @@
 // 8 slots that hold candidates: r = sqrtf(fl32(S)) correctly rounded, stored
 // in LDS as binary32 bits (which order like the distances, r >= 0).  The
 // candidate search walks batches of 4 columns of one row, in (row, column)
-// order: the smallest x distance of the batch plus the row's y distance is
-// summed exactly in binary64, the batch index fills the low bits of that sum
-// (always zero there), and one binary64 minimum selects the smallest distance
-// sum and, on ties, the first batch; within it the first column attaining
-// the batch's x minimum wins.  Slots keep the bins' order, so this is the
-// lowest centroid index among the smallest sums.
+// order: the smallest x distance of the batch plus the row's y distance, in
+// binary32, with the second smallest sum telling whether rounding could have
+// decided; near ties are searched again with exact binary64 sums.  Slots keep
+// the bins' order, so the result is the lowest centroid index among the
+// smallest sums.
 #pragma once
 
 #include <type_traits>
@@ -119,6 +118,26 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 // search needs the second smallest batch sum to exceed the smallest: at
 // least 7 by its error bound (see k_assign_mfma).
 constexpr int kFastGap = 8;
+// Low bits of the search's keys that hold the step of a lane's batch.
+constexpr int kStepBits = 4;
+static_assert(8 << kStepBits >= kMaxBatchLds, "eight batches per step");
+
+// Exchanges between the lanes of a wave: the upper half (the odd rows of 16
+// lanes) of a and the lower half (the even rows) of b swap places, so that a
+// lane of the lower half (an even row) gets both halves' a, the others both
+// halves' b; and x of the lane 8 further in the row.
+__device__ __forceinline__ u32x2 swap32(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_permlane32_swap(a, b, false, false);
+}
+__device__ __forceinline__ u32x2 swap16(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_permlane16_swap(a, b, false, false);
+}
+__device__ __forceinline__ uint32_t row_ror8(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, true);
+}
 
 // Row of the 32 x 32 MFMA result held by register r of a lane in group g.
 __device__ __forceinline__ constexpr int acc_row(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
@@ -759,16 +778,16 @@ template <typename T, int F>
 constexpr int kAssignWpb = 4 * kAssignWaves<T, F>;
 
 // LDS bytes of k_assign_mfma: palette operands, candidate batches, counts,
-// per wave x and y distances [32 slots][kKeyStride] (u32), then the
-// peak-extraction state (the searches merge their lanes' partial results in a
-// wave's y array once it is no longer read).  The summed vote histogram of
+// per wave x and y distances [32 slots][kKeyStride] (u32) and the far row,
+// then the peak-extraction state.  The summed vote histogram of
 // the prologue (kPadHist counts, 9 KB) shares its bytes with the first waves'
 // distance arrays, which are written only after it is no longer read.
+constexpr int kWaveKeys = (2 * kMfmaBins + 1) * kKeyStride;    // words
 template <int F>
 constexpr size_t kAssignLdsCore(int wpb)
 {
     return (size_t)kPopBytes<F> + (size_t)kMaxBatchLds * 24 + kMfmaBins * kMfmaBins * 4 +
-           (size_t)wpb * 2 * kMfmaBins * kKeyStride * 4 + sizeof(PeakLds) +
+           (size_t)wpb * kWaveKeys * 4 + sizeof(PeakLds) +
            (kMaxSlices + 1) * 4 + 16;
 }
 template <int F>
@@ -809,7 +828,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     constexpr int kWpb2 = kAssignWpb<T, F>;
     constexpr int kThreads = kWpb2 * 64;
     static_assert(kAssignLds<F>(kWpb2) <= 160 * 1024, "LDS of one compute unit");
-    static_assert(kPadHist * 8 <= kWpb2 * 2 * kMfmaBins * kKeyStride * 4, "the summed histogram fits in the waves' arrays");
+    static_assert(kPadHist * 8 <= kWpb2 * kWaveKeys * 4, "the summed histogram fits in the waves' arrays");
     // All LDS is static, so that table addresses are compile-time constants.
     __shared__ __align__(16) unsigned char smem[kAssignLds<F>(kWpb2)];
     uint32_t *s_pop = reinterpret_cast<uint32_t *>(smem);                            // palette operands
@@ -817,8 +836,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     uint32_t *s_bh = reinterpret_cast<uint32_t *>(s_bo + kMaxBatchLds);             // [kMaxBatchLds]
     uint32_t *s_bk = s_bh + kMaxBatchLds;                                            // [kMaxBatchLds]
     int32_t *s_cnt = reinterpret_cast<int32_t *>(s_bk + kMaxBatchLds);              // [1024]
-    uint32_t *s_keys = reinterpret_cast<uint32_t *>(s_cnt + kMfmaBins * kMfmaBins); // [kWpb2][2][32][kKeyStride]
-    PeakLds &pl = *reinterpret_cast<PeakLds *>(s_keys + kWpb2 * 2 * kMfmaBins * kKeyStride);
+    uint32_t *s_keys = reinterpret_cast<uint32_t *>(s_cnt + kMfmaBins * kMfmaBins); // [kWpb2][kWaveKeys]
+    PeakLds &pl = *reinterpret_cast<PeakLds *>(s_keys + kWpb2 * kWaveKeys);
     int *s_pref = reinterpret_cast<int *>(&pl + 1);                                  // [kMaxSlices + 1]
     int *s_next = s_pref + kMaxSlices + 1;                                            // next tile of the run
     long long *s_h = reinterpret_cast<long long *>(s_keys);                          // [kPadHist] summed votes
@@ -843,7 +862,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     // This wave's search arrays, [slot][kKeyStride] per axis: x key of column
     // slot j, pixel m at kx[j * kKeyStride + m], y distance of row slot j at
     // ky[...].
-    uint32_t *kx = s_keys + wv * 2 * kMfmaBins * kKeyStride;
+    uint32_t *kx = s_keys + wv * kWaveKeys;
     uint32_t *ky = kx + kMfmaBins * kKeyStride;
     for (int i = tid; i < kMfmaBins * kMfmaBins; i += kThreads) s_cnt[i] = 0;
     if (tid == 0) *s_next = 0;
@@ -870,7 +889,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     peaks_lds_find<kWpb2>(pb, cut, cap, s_h, pl, s_bo, s_bh, s_bk, [&]() {
         if (t < tend) raw.load(emb + (size_t)ip * dstride, yoff, g);
     });
-    // s_h is read; its bytes become distance arrays
+    // s_h is read; its bytes become distance arrays, each with its far row
+    if (lane < 32) kx[2 * kMfmaBins * kKeyStride + lane] = kFarBits;
     const int Kc = pl.Kc;
     if (blockIdx.x == 0) {
 #pragma unroll
@@ -953,208 +973,159 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         }
     };
 
-    // Candidate search.  Lane l serves the four pixels 4 q .. 4 q + 3
-    // (q = l & 7) for the batches j, j + 8, ... (j = l >> 3): one 16-byte
-    // read fetches a column's distances of its four pixels, so each address
-    // computation and each read serve four pixels.  Per batch and pixel the
-    // smallest of the 4 x distances plus the row's y distance, summed exactly
-    // in binary64, has at least 12 zero bits at the bottom of its mantissa
-    // (both distances are 0 or binary32 values of at least 2^-7, so the sum is
-    // a multiple of 2^-30 below 2^10), which take the batch index (< 128).  The
-    // eight lanes of a pixel quad then combine their minima through LDS; lane
-    // m takes pixel m's result, finds the first column of the winning batch
-    // with the batch's smallest x distance, and (lanes of half 0, valid
-    // pixels) writes its label.
-    auto search = [&](int pix, int nvalid) {
-        __builtin_amdgcn_wave_barrier();
-        const int q = lane & 7, j0 = lane >> 3;
-        const unsigned char *kxq = reinterpret_cast<const unsigned char *>(kx + 4 * q);
-        const unsigned char *kyq = reinterpret_cast<const unsigned char *>(ky + 4 * q);
-        double b4[4] = {__builtin_inf(), __builtin_inf(), __builtin_inf(), __builtin_inf()};
-        u32x4 o = s_bo[j0];                         // j0 < 8 <= nbat
-        uint32_t hb = s_bh[j0];
-        for (int bi = j0; bi < nbat; bi += 8) {     // nbat is a multiple of 8: the same count for every lane
-            const u32x4 v0 = *reinterpret_cast<const u32x4 *>(kxq + o.x);
-            const u32x4 v1 = *reinterpret_cast<const u32x4 *>(kxq + o.y);
-            const u32x4 v2 = *reinterpret_cast<const u32x4 *>(kxq + o.z);
-            const u32x4 v3 = *reinterpret_cast<const u32x4 *>(kxq + o.w);
-            const u32x4 yd = *reinterpret_cast<const u32x4 *>(kyq + hb);
-            if (bi + 8 < nbat) {                    // the next batch's offsets, read ahead
-                o = s_bo[bi + 8];
-                hb = s_bh[bi + 8];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const uint32_t m = min(min(v0[e], v1[e]), min(v2[e], v3[e]));
-                const double sum = (double)__uint_as_float(m) + (double)__uint_as_float(yd[e]);
-                const unsigned long long sb = (unsigned long long)__double_as_longlong(sum);
-                const unsigned long long key = (sb & ~0xffffffffull) | ((uint32_t)sb | (uint32_t)bi);
-                b4[e] = min_f64(b4[e], __longlong_as_double((long long)key));
-            }
+    // Label and score of pixel `pix`, whose nearest candidate k has the exact
+    // distance sum D (Eq8).
+    auto put = [&](int pix, int k, double D) {
+        if (D < tau32) {
+            labels[pix] = k + 1;
+            if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-5));
+            atomicAdd(s_cnt + k, 1);
+        } else {
+            labels[pix] = 0;
+            if (score_map) score_map[pix] = 0.0f;
         }
-        // the eight lanes of a pixel quad combine through LDS (the y array
-        // is no longer read): pixel m's partial key j at double 9 m + j (an
-        // odd pixel stride spreads the banks); half g of the wave takes
-        // j = 4g .. 4g + 3 for pixel m = lane & 31, then the halves exchange
-        __builtin_amdgcn_wave_barrier();
-        double *part = reinterpret_cast<double *>(ky);
-#pragma unroll
-        for (int e = 0; e < 4; e++) part[(4 * q + e) * 9 + j0] = b4[e];
-        __builtin_amdgcn_wave_barrier();
-        double bm = part[ln * 9 + 4 * g];
-#pragma unroll
-        for (int jj = 1; jj < 4; jj++) bm = min_f64(bm, part[ln * 9 + 4 * g + jj]);
-        bm = min_f64(bm, __shfl_xor(bm, 32));
-        __builtin_amdgcn_wave_barrier();
-        const unsigned long long best = (unsigned long long)__double_as_longlong(bm);
-        const int bi = (int)((uint32_t)best & 127u);
-        const double D = __longlong_as_double((long long)(best & ~127ull));
-        const u32x4 ow = s_bo[bi];
-        const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + ln);
-        const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + ow.x);
-        const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + ow.y);
-        const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + ow.z);
-        const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + ow.w);
-        const uint32_t wm = min(min(w0, w1), min(w2, w3));
-        // the batch's first column at its minimum
-        const int k = (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
-        if (g == 0 && ln < nvalid) {
-            if (D < tau32) {      // Eq8
-                labels[pix] = k + 1;
-                if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-5));
-                atomicAdd(s_cnt + k, 1);
-            } else {
-                labels[pix] = 0;
-                if (score_map) score_map[pix] = 0.0f;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
     };
 
-    // Fast search (labels only: no score map, tau = +inf).  The distances
-    // are the hardware square roots r~ of fl32(S), each within one binary32
-    // step of the correctly rounded r (cpe_check_sqrt verifies the step
-    // correction of sqrt_cr, which only tries r~ and its two neighbours, on
-    // every input).  Lane l serves the pixels 4q .. 4q + 3 (q = l & 7) over
-    // the batches j, j + 8, ... (j = l >> 3) of the unpadded list, so that no
-    // batch is seen twice (one 16-byte read fetches a column's distances of
-    // its four pixels; the next batch's offsets are read ahead), and keeps
-    // per pixel the smallest binary32 sum fl(min x~ + y~) of a batch, its
-    // batch, and the second smallest.  A step at v is at most 2^-23 v, so
-    // x~ + y~ lies within relative 2^-23 of x + y and the rounded sum s
-    // within relative g = 3 2^-24 + 2^-47 of the batch's true minimum D.
-    // If the second smallest sum exceeds the smallest s_w by kFastGap steps
-    // (each more than 2^-24 s_w), so by more than 2g / (1 - g) s_w, every
-    // other batch's D exceeds the winning batch's (a sum of 0 is exact: any
-    // other distance sum is at least 2^-7).
-    // Within the winning batch (one row, exact distances of one y), a column
-    // whose r~ is at least 3 steps above the batch's smallest r~ is strictly
-    // farther.  When both hold the winner is the unique minimiser of the
-    // exact sums, i.e. the candidate the exact search selects.  Otherwise
-    // (near ties, within a few units in the last place) the wave recomputes
-    // the tile exactly; false is returned and nothing is written.
-    const int nbr = min(pl.nbat_real, kMaxBatchLds);
-    auto search_fast = [&](int pix, int nvalid) -> bool {
+    // Candidate search of one tile from the distance arrays; false, with
+    // nothing written, if a pixel is not decided.  Lane l serves the four
+    // pixels 4 q .. 4 q + 3 (q = l & 7) over the batches j, j + 8, ... (j =
+    // l >> 3): one 16-byte read fetches a column's distances of its four
+    // pixels, and the next batch's offsets are read ahead.  Per pixel it keeps
+    // the smallest binary32 sum s = fl(min x + y) of a batch and the second
+    // smallest, as keys: the bits of s (which order like the sums) with the
+    // batch's step in the low kStepBits.  The first batch only initialises.
+    // The eight lanes of a pixel quad then merge in registers (half and row
+    // swaps that leave a lane two pixels, one, then a rotation within the row
+    // of 16), which leaves pixel m = 4 q + 2 (l >> 5) + (l >> 4 & 1) in lane l
+    // and the arrays intact.
+    //
+    // Let every x and y be within one binary32 step (at most 2^-23 of the
+    // value) of the correctly rounded root: the hardware's root is
+    // (cpe_check_sqrt verifies sqrt_cr, which only tries it and its two
+    // neighbours, on every input).  Then x + y lies within relative 2^-23 of
+    // the exact sum, and s within g = 3 2^-24 + 2^-47 of the batch's true
+    // minimum D.  If every other batch's s exceeds the winner's s_w by
+    // kFastGap steps (each more than 2^-24 s_w), so by more than 2g / (1 - g)
+    // s_w, its D is strictly larger (a sum of 0 is exact: any other distance
+    // sum is at least 2^-7).  The keys show a gap of s less the step bits.
+    // (Merging through LDS, with the batch in a register of its own per pixel
+    // and the binary64 sums in the exact kernel, took 43 VALU instructions per
+    // step instead of 31 and two LDS round trips more: 1024 x 2048, 16
+    // harmonics, fp16, 78.0 against 74.3 us per frame; 2160 x 3840 with 8
+    // 239 against 228.)
+    // Within the winning batch (one row, one y) a column 3 steps above the
+    // smallest is strictly farther.  So a decided pixel has the label of the
+    // exact sums.  EXACT (correctly rounded roots): the first column at the
+    // batch's smallest x is the nearest, and its D is exact.
+    auto search = [&](auto exact, int pix, int nvalid) -> bool {
+        constexpr bool kExact = decltype(exact)::value;
+        constexpr uint32_t kStepMask = (1u << kStepBits) - 1u;
         __builtin_amdgcn_wave_barrier();
         int lo = lane;
         __asm__ volatile("" : "+v"(lo));        // recomputed per tile, not held across the loop
         const int q = lo & 7, j0 = lo >> 3;
         const unsigned char *kxq = reinterpret_cast<const unsigned char *>(kx + 4 * q);
         const unsigned char *kyq = reinterpret_cast<const unsigned char *>(ky + 4 * q);
-        float b[4], s2[4];
-        int bx[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            b[e] = s2[e] = __builtin_inff();
-            bx[e] = 0;
-        }
-        u32x4 o = {};
-        uint32_t hb = 0;
-        if (j0 < nbr) {
-            o = s_bo[j0];
-            hb = s_bh[j0];
-        }
-        for (int bi = j0; bi < nbr; bi += 8) {
+        uint32_t b[4], s2[4];
+        u32x4 o = s_bo[j0];                     // j0 < 8 <= nbat
+        uint32_t hb = s_bh[j0];
+        // the sums of the batch at o, hb; then the offsets of batch `next`
+        // (past the list: bytes of the arrays behind it, never used)
+        auto sums = [&](int next, uint32_t (&sm)[4]) {
             const u32x4 v0 = *reinterpret_cast<const u32x4 *>(kxq + o.x);
             const u32x4 v1 = *reinterpret_cast<const u32x4 *>(kxq + o.y);
             const u32x4 v2 = *reinterpret_cast<const u32x4 *>(kxq + o.z);
             const u32x4 v3 = *reinterpret_cast<const u32x4 *>(kxq + o.w);
             const u32x4 yd = *reinterpret_cast<const u32x4 *>(kyq + hb);
-            if (bi + 8 < nbr) {             // the next batch's offsets, read ahead
-                o = s_bo[bi + 8];
-                hb = s_bh[bi + 8];
-            }
+            o = s_bo[next];
+            hb = s_bh[next];
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 const uint32_t m = min(min(v0[e], v1[e]), min(v2[e], v3[e]));
-                const float sm = __uint_as_float(m) + __uint_as_float(yd[e]);
-                s2[e] = __builtin_amdgcn_fmed3f(b[e], s2[e], sm);
-                bx[e] = sm < b[e] ? bi : bx[e];
-                b[e] = sm < b[e] ? sm : b[e];
+                sm[e] = __float_as_uint(__uint_as_float(m) + __uint_as_float(yd[e])) & ~kStepMask;
+            }
+        };
+        sums(j0 + 8, b);
+#pragma unroll
+        for (int e = 0; e < 4; e++) s2[e] = 0x7f800000u;
+        for (int it = 1; 8 * it < nbat; it++) {
+            uint32_t sm[4];
+            sums(8 * it + 8 + j0, sm);
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const uint32_t key = sm[e] | (uint32_t)it;
+                s2[e] = max(min(b[e], s2[e]), min(max(b[e], s2[e]), key));      // their median
+                b[e] = min(b[e], key);
             }
         }
-        // the eight lanes of a pixel quad combine through LDS (the y array
-        // is no longer read): pixel m's partial j (smallest, second, batch)
-        // at word 25 m + 3 j (an odd pixel stride spreads the banks); half g
-        // of the wave merges j = 4g .. 4g + 3 for pixel m = lane & 31, then
-        // the two halves exchange (as bit patterns, which order like the
-        // non-negative sums; equal smallest sums leave a second smallest
-        // equal to the smallest)
-        __builtin_amdgcn_wave_barrier();
-        uint32_t *part = ky;
+        // merge (b, s2, lane j) of two parts of one pixel's batches
+        struct Part {
+            uint32_t b, s2, j;
+        };
+        auto merge = [](Part u, Part v) -> Part {
+            Part r;
+            r.j = v.b < u.b ? v.j : u.j;
+            r.s2 = min(min(u.s2, v.s2), max(u.b, v.b));
+            r.b = min(u.b, v.b);
+            return r;
+        };
+        Part p[2];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            uint32_t *w = part + (4 * q + e) * 25 + 3 * j0;
-            w[0] = __float_as_uint(b[e]);
-            w[1] = __float_as_uint(s2[e]);
-            w[2] = (uint32_t)bx[e];
+        for (int e = 0; e < 2; e++) {           // pixel e in half 0, e + 2 in half 1; j bit 2
+            const u32x2 bb = swap32(b[e], b[e + 2]), ss = swap32(s2[e], s2[e + 2]);
+            p[e] = merge({bb[0], ss[0], (uint32_t)j0 & 3u}, {bb[1], ss[1], (uint32_t)j0 | 4u});
         }
-        __builtin_amdgcn_wave_barrier();
-        uint32_t ub = 0xffffffffu, us = 0xffffffffu, ux = 0;
-#pragma unroll
-        for (int jj = 0; jj < 4; jj++) {
-            const uint32_t *rp = part + ln * 25 + 3 * (4 * g + jj);
-            const u32x4 r = {rp[0], rp[1], rp[2], 0u};
-            us = min(min(us, r.y), max(ub, r.x));
-            ux = r.x < ub ? r.z : ux;
-            ub = min(ub, r.x);
+        {                                       // pixel + 0 in even rows of 16, + 1 in odd ones; j bit 1
+            const u32x2 bb = swap16(p[0].b, p[1].b), ss = swap16(p[0].s2, p[1].s2), jj = swap16(p[0].j, p[1].j);
+            p[0] = merge({bb[0], ss[0], jj[0]}, {bb[1], ss[1], jj[1]});
         }
-        {
-            const uint32_t ob = __shfl_xor(ub, 32), os = __shfl_xor(us, 32), ox = __shfl_xor(ux, 32);
-            us = min(min(us, os), max(ub, ob));
-            ux = ob < ub ? ox : ux;
-            ub = min(ub, ob);
-        }
-        __builtin_amdgcn_wave_barrier();
-        const int bi = (int)ux;
+        p[0] = merge(p[0], {row_ror8(p[0].b), row_ror8(p[0].s2), row_ror8(p[0].j)});   // j bit 0
+        const int m = 4 * q + 2 * (lo >> 5) + ((lo >> 4) & 1);
+        const int pm = __shfl(pix, m);
+        const int bi = (int)(8u * (p[0].b & kStepMask) + p[0].j);
         const u32x4 ow = s_bo[bi];
-        const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + ln);
+        const int k0 = (int)s_bk[bi];
+        const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + m);
         const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + ow.x);
         const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + ow.y);
         const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + ow.z);
         const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + ow.w);
-        const uint32_t wm = min(min(w0, w1), min(w2, w3));
-        const uint32_t oc = w0 == wm ? ow.x : w1 == wm ? ow.y : w2 == wm ? ow.z : ow.w;   // first column at the minimum
-        const bool near = (ow.x != oc && w0 - wm < 3u) || (ow.y != oc && w1 - wm < 3u) ||
-                          (ow.z != oc && w2 - wm < 3u) || (ow.w != oc && w3 - wm < 3u);
-        const bool amb = near || us - ub < (uint32_t)kFastGap;
-        const bool valid = g == 0 && ln < nvalid;
+        const uint32_t l01 = min(w0, w1), l23 = min(w2, w3), wm = min(l01, l23);
+        const int k = k0 + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
+        bool amb = (p[0].s2 >> kStepBits) - (p[0].b >> kStepBits) <
+                   (uint32_t)(kFastGap + 2 * (int)kStepMask) >> kStepBits;
+        if constexpr (!kExact) {
+            const uint32_t second = min(min(max(w0, w1), max(w2, w3)), max(l01, l23));
+            amb |= second - wm < 3u;
+        }
+        // one of the two lanes that hold the pixel
+        const bool valid = (lo & 8) == 0 && m < nvalid;
         if (force_exact || __ballot(amb && valid)) return false;
         if (valid) {
-            const int k = (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
-            labels[pix] = k + 1;
-            atomicAdd(s_cnt + k, 1);
+            if constexpr (kExact) {
+                const uint32_t y = *reinterpret_cast<const uint32_t *>(
+                    reinterpret_cast<const unsigned char *>(ky + m) + s_bh[bi]);
+                const double D = (double)__uint_as_float(wm) + (double)__uint_as_float(y);
+                put(pm, k, D);
+            } else {
+                labels[pm] = k + 1;
+                atomicAdd(s_cnt + k, 1);
+            }
         }
         __builtin_amdgcn_wave_barrier();
         return true;
     };
 
-    // Exact search of the tiles the fast search leaves undecided: lane m
-    // (either half: half g takes the batches g, g + 2, ...) scans every batch
-    // for pixel m with the keys of the exact search above (binary64 sum of
-    // the batch's smallest x distance and the row's y distance, batch index
-    // in the low bits), then takes the first column of the winning batch at
-    // the batch's minimum: the same candidate as the exact search.
+    // The tiles that the search leaves undecided, from exact distances: lane
+    // m (either half: half g takes the batches g, g + 2, ...) scans every
+    // batch for pixel m.  The smallest x distance of a batch plus the row's y
+    // distance, summed exactly in binary64, has at least 12 zero bits at the
+    // bottom of its mantissa (both distances are 0 or binary32 values of at
+    // least 2^-7, so the sum is a multiple of 2^-30 below 2^10), which take the
+    // batch index (< 128): one binary64 minimum selects the smallest sum and,
+    // on ties, the first batch, and its first column at the batch's minimum
+    // is the lowest candidate index.
+    const int nbr = min(pl.nbat_real, kMaxBatchLds);
     auto search_pix = [&](int pix, int nvalid) {
         __builtin_amdgcn_wave_barrier();
         const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + ln);
@@ -1173,18 +1144,17 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
             best = min_f64(best, __longlong_as_double((long long)((sb & ~0xffffffffull) | ((uint32_t)sb | (uint32_t)bi))));
         }
         best = min_f64(best, __shfl_xor(best, 32));
-        const int bi = (int)((uint32_t)__double_as_longlong(best) & 127u);
+        const unsigned long long key = (unsigned long long)__double_as_longlong(best);
+        const int bi = (int)((uint32_t)key & 127u);
         const u32x4 o = s_bo[bi];
         const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + o.x);
         const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + o.y);
         const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + o.z);
         const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + o.w);
         const uint32_t wm = min(min(w0, w1), min(w2, w3));
-        if (g == 0 && ln < nvalid) {
-            const int k = (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
-            labels[pix] = k + 1;
-            atomicAdd(s_cnt + k, 1);
-        }
+        if (g == 0 && ln < nvalid)
+            put(pix, (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3),
+                __longlong_as_double((long long)(key & ~127ull)));
         __builtin_amdgcn_wave_barrier();
     };
 
@@ -1206,7 +1176,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const int nvalid = min(32, n - 32 * t);
         if constexpr (FAST) {
             distances(std::false_type{}, raw, next);
-            if (!search_fast(ip, nvalid)) {
+            if (!search(std::false_type{}, ip, nvalid)) {
                 raw.load(emb + (size_t)ip * dstride, yoff, g);          // this tile's rows again
                 distances(std::true_type{}, raw, []() {});
                 if (tn < tend) raw.load(emb + (size_t)ipn * dstride, yoff, g);   // the next tile's rows again
@@ -1214,7 +1184,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
             }
         } else {
             distances(std::true_type{}, raw, next);
-            search(ip, nvalid);
+            if (!search(std::true_type{}, ip, nvalid)) search_pix(ip, nvalid);
         }
         t = tn;
         tn = tnn;

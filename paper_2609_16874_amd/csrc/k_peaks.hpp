@@ -14,12 +14,12 @@
 //                 K, the compact list and the summed histogram to memory.
 //
 // Candidate batches.  The first min(K, cap) candidates are grouped by row b
-// into batches of 4 columns (a row's last batch repeats its last column,
-// which leaves a minimum unchanged).  Batch i is bo[i] = the byte offsets
+// into batches of 4 columns (a row's last batch is filled with the far row,
+// which never attains a minimum).  Batch i is bo[i] = the byte offsets
 // 128 j of its 4 column slots j in the assignment kernel's [slot][32 pixels]
 // x array, bh[i] the byte offset of its row's slot in the y array, and bk[i]
 // the index of its first candidate.  The list is padded to a multiple of 8
-// batches with copies of its last one.
+// batches of the far row.
 #pragma once
 
 #include "cpe_common.hpp"
@@ -119,6 +119,10 @@ constexpr int kLdsPeakBins = 32;
 constexpr int kMaxBatchLds = 128;   // <= 16 strict maxima per row of 32 -> <= 4 batches per row
 constexpr int kBatchPad = 8;        // the batch list is padded to a multiple of this
 constexpr int kKeyStride = 32;      // words per bin row of the assignment kernel's key arrays
+// Byte offsets of the far row, kFarBits (2^126) for every pixel, which follows
+// the x and y arrays of 32 slots each: from the x and from the y array.
+constexpr uint32_t kFarX = 2 * 32 * 4 * kKeyStride, kFarY = kFarX / 2;
+constexpr uint32_t kFarBits = 0x7e800000u;
 constexpr int kPadRow = kLdsPeakBins + 2;                  // the summed histogram in LDS: rows of 34 counts,
 constexpr int kPadHist = kPadRow * (kLdsPeakBins + 2);     //   a border of -1 around the 32 x 32 bins
 
@@ -244,30 +248,26 @@ __device__ __forceinline__ void peaks_lds_find(const PeakBins<WAVES> &pb, long l
         const int start = incl - nbt, total = __builtin_amdgcn_readlane(incl, kLdsPeakBins - 1);
         const int padded = (total + kBatchPad - 1) & ~(kBatchPad - 1);
         const uint32_t hb = (uint32_t)rslot * (4u * kKeyStride);
-        uint32_t last = 0;
-        u32x4_pk o = {0u, 0u, 0u, 0u};
         for (int j = 0; j < nbt; j++) {
+            u32x4_pk o;
 #pragma unroll
             for (int s4 = 0; s4 < 4; s4++) {
+                o[s4] = kFarX;
                 if (m) {
                     const int a = __builtin_ctz(m);
-                    last = (uint32_t)__popc(cm & ((1u << a) - 1u)) * (4u * kKeyStride);
+                    o[s4] = (uint32_t)__popc(cm & ((1u << a) - 1u)) * (4u * kKeyStride);
                     m &= m - 1u;
                 }
-                o[s4] = last;
             }
             s_bo[start + j] = o;
             s_bh[start + j] = hb;
             s_bk[start + j] = (uint32_t)(first + 4 * j);
         }
-        // pad the list with copies of the last batch (a repeated batch leaves
-        // every minimum unchanged)
-        if (nbt > 0 && start + nbt == total)
-            for (int e = total; e < padded; e++) {
-                s_bo[e] = o;
-                s_bh[e] = hb;
-                s_bk[e] = (uint32_t)(first + 4 * (nbt - 1));
-            }
+        if (b < padded - total) {
+            s_bo[total + b] = u32x4_pk{kFarX, kFarX, kFarX, kFarX};
+            s_bh[total + b] = kFarY;
+            s_bk[total + b] = 0u;
+        }
         if (tid == 0) {
             pl.K = K;
             pl.Kc = K < cap ? K : cap;

@@ -17,8 +17,16 @@ namespace cpe {
 constexpr int64_t kVoteGrid = 256;
 constexpr int64_t kAssignGrid = 256;
 // Frames from this many pixels take the fast assignment search when only
-// labels are requested.
-constexpr int64_t kFastSearchPixels = 1 << 20;
+// labels are requested: where a wave has more than one tile the shorter
+// instruction stream pays, below it a near tie's second pass costs more.
+// Measured (exact, fast search, us per frame): 8 harmonics or fewer, 256 x 256
+// fp32 18.8, 19.6; 512 x 512 fp32 24.0, 24.1; 479 x 641 fp16 32.1, 30.2; 704 x
+// 704 fp32 30.6, 28.9; above, 512 x 520 fp16 24.0, 24.2; 640 x 640 fp16 29.3,
+// 29.2; 900 x 900 fp16 41.1, 39.9.
+// fp32 inputs with more than 8 harmonics spill registers in the fast kernel
+// (640 x 640: 36.4, 39.4) and keep the exact one.
+template <typename T, int F>
+constexpr int64_t kFastSearchPixels = F <= 8 ? 1LL << 18 : sizeof(T) == 2 ? 1LL << 19 : INT64_MAX;
 
 // Largest pixel tile (threads per block) whose LDS footprint fits the budget.
 inline int pick_tile(size_t fixed, size_t per_px, size_t budget)
@@ -141,7 +149,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         // fast search, which pays off when every wave has several tiles (it
         // shortens each tile's work but lengthens its dependency chain)
         const bool labels_only = score == nullptr && !(fa.tau4096 < __builtin_inf());
-        const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels);
+        const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels<T, F>);
         auto assign_kernel = fast ? k_assign_mfma<T, F, true> : k_assign_mfma<T, F, false>;
         if (!launch(2, assign_kernel, dim3(grid2), dim3(wpb2 * 64), 0, e, dstride, yoff, (const int32_t *)list,
                     (const int32_t *)sc.counts, nslices, slice_px, npix, fa.tau4096 * 0x1p-7, h->tb,

@@ -48,6 +48,26 @@ def test_every_partial_sum_is_exact():
     assert r < 2 ** 24 and a < 2 ** 24, (r, a)
 
 
+def test_search_keys_keep_the_fast_gap():
+    """The assignment search compares sums whose low kStepBits are replaced
+    by a step number: a pixel that its test decides has batch sums at least
+    kFastGap binary32 steps apart, and the winner's key is the smaller sum."""
+    with open(os.path.join(_CSRC, "k_mfma.hpp")) as fh:
+        src = fh.read()
+    gap, bits = (int(re.search(rf"constexpr int {n} = (\d+);", src).group(1)) for n in ("kFastGap", "kStepBits"))
+    need = (gap + 2 * ((1 << bits) - 1)) >> bits
+    rng = np.random.default_rng(5)
+    s = rng.integers(0x3c000000, 0x44000000, 400000)
+    t = s + rng.integers(-64, 65, s.size)
+    key = lambda v: (v >> bits << bits) | rng.integers(0, 1 << bits, v.size)
+    ks, kt = key(s), key(t)
+    lo, hi = np.minimum(ks, kt), np.maximum(ks, kt)
+    decided = (hi >> bits) - (lo >> bits) >= need
+    assert 0.2 < decided.mean() < 0.9
+    assert ((t - s)[decided & (ks < kt)] >= gap).all()
+    assert ((s - t)[decided & (kt < ks)] >= gap).all()
+
+
 def _values(rng, dtype, shape):
     """Channels that reach every branch of the input conversion."""
     n = int(np.prod(shape))
