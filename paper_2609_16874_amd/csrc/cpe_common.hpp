@@ -31,11 +31,6 @@ typedef short v2s __attribute__((ext_vector_type(2)));
 
 // Device-resident constants built once by cpe_decode_create.
 struct Tables {
-    const int32_t *pal_x;     // [Bw][F]: harmonic k = (sin | cos << 16), int16 each, x4096
-    const int32_t *pal_y;     // [Bh][F]
-    const uint32_t *n2_x;     // [Bw] sum of squared palette entries
-    const uint32_t *n2_y;     // [Bh]
-    const uint16_t *wt;       // [kWKeys] 2^15 e^-d per 8-bit bucket (bucket order)
     const float *cx;          // [Bw] bin centres (pixels)
     const float *cy;          // [Bh]
     // matrix-core path
@@ -46,15 +41,6 @@ struct Tables {
     const uint16_t *wt_pk;    // [kWKeys] weight q = lo - 256 nh as int8 limbs lo | nh << 8 (lo >= -128, nh <= 0),
                               //          at LDS position ((e + 17) & 31) * 256 + t
 };
-
-// Input to fixed point: rint(4096 clamp(v, -1.5, 1.5)), the input on the
-// palette's grid of 1/4096; a NaN clamps to -1.5 (fmaxf/fminf return the
-// non-NaN operand).
-__device__ __forceinline__ int32_t to_fixed(float v)
-{
-    const float c = fminf(fmaxf(v, -1.5f), 1.5f);
-    return (int32_t)rintf(c * 4096.0f);
-}
 
 // The Eq4 distance in units of 1/4096: the correctly rounded binary32 square
 // root of x = fl32(S) (0 or at least 1).  The hardware square root is within
@@ -85,11 +71,6 @@ __device__ __forceinline__ double min_f64(double a, double b)
     return r;
 }
 
-__device__ __forceinline__ int32_t pack2(int32_t lo, int32_t hi)
-{
-    return (int32_t)(((uint32_t)lo & 0xffffu) | ((uint32_t)hi << 16));
-}
-
 __device__ __forceinline__ float half_bits_to_float(uint32_t bits)
 {
     return (float)__builtin_bit_cast(_Float16, (uint16_t)bits);
@@ -98,29 +79,6 @@ __device__ __forceinline__ float half_bits_to_float(uint32_t bits)
 template <typename T> __device__ __forceinline__ float load_scalar(const T *p);
 template <> __device__ __forceinline__ float load_scalar<float>(const float *p) { return *p; }
 template <> __device__ __forceinline__ float load_scalar<_Float16>(const _Float16 *p) { return (float)*p; }
-
-// Foreground value of pixel p.  Without a foreground channel (fg == nullptr,
-// a uniform branch) every pixel participates: +inf exceeds any finite
-// threshold.
-template <typename T>
-__device__ __forceinline__ float fg_value(const T *fg, int64_t p)
-{
-    return fg ? load_scalar<T>(fg + p) : __builtin_huge_valf();
-}
-
-// S = |X|^2 + |P|^2 - 2 X.P is exact modulo 2^32 and lies in [0, 2^32).
-__device__ __forceinline__ uint32_t axis_s(uint32_t nX, uint32_t nP, int32_t dot)
-{
-    return nX + nP - 2u * (uint32_t)dot;
-}
-
-// m-bit distance bucket: exponent and top m mantissa bits of fl32(S+1).
-template <int M>
-__device__ __forceinline__ int dist_key(uint32_t s)
-{
-    const uint32_t bits = __float_as_uint((float)(s + 1u));
-    return (int)(bits >> (23 - M)) - (127 << M);
-}
 
 // Inclusive prefix sum of x over the 64 lanes of a wave with DPP moves:
 // shifts by 1, 2, 4, 8 within each row of 16 lanes, then the last lane of
@@ -145,6 +103,17 @@ __device__ __forceinline__ uint32_t wave_or32(uint32_t x)
     x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);   // row_shr:4
     x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);   // row_shr:8
     return (uint32_t)(__builtin_amdgcn_readlane((int)x, 15) | __builtin_amdgcn_readlane((int)x, 31));
+}
+
+// Bitwise or of x over a wave (every lane active).
+__device__ __forceinline__ uint32_t wave_or64(uint32_t x)
+{
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
+    return (uint32_t)(__builtin_amdgcn_readlane((int)x, 15) | __builtin_amdgcn_readlane((int)x, 31) |
+                      __builtin_amdgcn_readlane((int)x, 47) | __builtin_amdgcn_readlane((int)x, 63));
 }
 
 __device__ __forceinline__ int lane_prefix(unsigned long long mask)

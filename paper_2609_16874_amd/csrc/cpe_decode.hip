@@ -10,10 +10,11 @@
 //   compact participating-pixel list, vote histograms cleared (k_compact);
 //   vote    per-pixel recovery + soft voting into replicated 64-bit histograms
 //           (k_vote_mfma, one pass per block of 32 x 32 bins);
-//   peaks   local-maxima search and compaction (k_peaks, grids above 32 x 32);
+//   peaks   local-maxima search and the assignment's plan (k_peaks, grids
+//           above 32 x 32);
 //   assign  nearest-candidate assignment, label and score write-out, pixel
 //           counts (k_assign_mfma, whose workgroups extract the peaks in
-//           their prologue, for grids up to 32 x 32; k_assign_generic above).
+//           their prologue, for grids up to 32 x 32; k_assign_big above).
 // cpe_decode_masks expands a label map into binary masks (masks.hip).
 
 #include <hip/hip_runtime.h>
@@ -27,6 +28,7 @@
 
 #include "cpe_decoder.hpp"
 #include "k_compact.hpp"
+#include "k_peaks.hpp"
 
 using namespace cpe;
 
@@ -101,9 +103,8 @@ constexpr int kStaticMaxBins = kMaxBins * kMaxBins;
 constexpr size_t kStaticSet = (size_t)kReplicas * kStaticMaxBins;                // words per histogram set
 constexpr size_t kStaticHrep = 0;                                               // [2][kReplicas][bins]
 constexpr size_t kStaticHlast = kStaticHrep + 2 * kStaticSet * 8;
-constexpr size_t kStaticPeaks = kStaticHlast + (size_t)kStaticMaxBins * 8;
-constexpr size_t kStaticKinfo = kStaticPeaks + (size_t)kStaticMaxBins * 4;
-constexpr size_t kStaticCounts = kStaticKinfo + 256;
+constexpr size_t kStaticPlan = kStaticHlast + (size_t)kStaticMaxBins * 8;
+constexpr size_t kStaticCounts = (kStaticPlan + plan_bytes(kMaxBins, kMaxBins) + 255) & ~(size_t)255;
 constexpr size_t kStaticList = kStaticCounts + (size_t)kMaxSlices * 4;
 constexpr size_t kStaticBytes = kStaticList + (size_t)list_entries(kStaticMaxPixels) * 4;
 static_assert(kStaticMaxPixels <= (int64_t)kMaxSlices * kCompactSpan, "one compaction step per slice: one slice "
@@ -153,8 +154,7 @@ Scratch static_layout(unsigned char *base, int dev)
     sc.parity = &g_parity[dev];
     sc.dirty = g_dirty[dev];
     sc.hlast = reinterpret_cast<unsigned long long *>(base + kStaticHlast);
-    sc.peaks = reinterpret_cast<int32_t *>(base + kStaticPeaks);
-    sc.kinfo = reinterpret_cast<int32_t *>(base + kStaticKinfo);
+    sc.plan = reinterpret_cast<BigPlan *>(base + kStaticPlan);
     sc.counts = reinterpret_cast<int32_t *>(base + kStaticCounts);
     sc.list = reinterpret_cast<int32_t *>(base + kStaticList);
     return sc;
@@ -259,23 +259,20 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
         wt_pk[(((e + 17) & 31) << kWMant) | t] = (uint16_t)((lo & 255) | (nh & 255) << 8);
     }
 
-    auto pack = [&](int n, const std::vector<int16_t> &pal, std::vector<int32_t> &pk, std::vector<uint32_t> &n2) {
-        pk.assign((size_t)n * F, 0);
+    auto norms = [&](int n, const std::vector<int16_t> &pal, std::vector<uint32_t> &n2) {
         n2.assign(n, 0);
         for (int a = 0; a < n; a++) {
             uint32_t s = 0;
             for (int k = 0; k < F; k++) {
                 const int16_t lo = pal[(size_t)a * twoF + 2 * k], hi = pal[(size_t)a * twoF + 2 * k + 1];
-                pk[(size_t)a * F + k] = (int32_t)(((uint32_t)(uint16_t)lo) | ((uint32_t)(uint16_t)hi << 16));
                 s += (uint32_t)(lo * lo) + (uint32_t)(hi * hi);
             }
             n2[a] = s;
         }
     };
-    std::vector<int32_t> pkx, pky;
     std::vector<uint32_t> n2x, n2y;
-    pack(bins_w, h->pal_x, pkx, n2x);
-    pack(bins_h, h->pal_y, pky, n2y);
+    norms(bins_w, h->pal_x, n2x);
+    norms(bins_h, h->pal_y, n2y);
 
     // matrix-core operands: -2P = kDistBase hi + lo with |lo| <= kDistBase / 2,
     // as binary16 MFMA operands [axis][block of 32 bins][kind][64 lanes][8]:
@@ -335,16 +332,12 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
         off = align_up(off + bytes, 256);
         return o;
     };
-    const size_t o_px = carve(pkx.size() * 4), o_py = carve(pky.size() * 4);
-    const size_t o_nx = carve(n2x.size() * 4), o_ny = carve(n2y.size() * 4);
-    const size_t o_wt = carve(kWKeys * 2);
     const size_t o_cx = carve(cx.size() * 4), o_cy = carve(cy.size() * 4);
     const size_t o_pop = carve(pop.size() * 2);
     const size_t o_wpk = carve(wt_pk.size() * 2);
     const size_t o_hrep = carve(2 * (size_t)kReplicas * nb * 8);
     const size_t o_hlast = carve((size_t)nb * 8);
-    const size_t o_peaks = carve((size_t)centroid_capacity * 4);
-    const size_t o_kinfo = carve(16);
+    const size_t o_plan = carve(bins_w > kMfmaBins || bins_h > kMfmaBins ? plan_bytes(bins_w, bins_h) : 0);
     const size_t o_count = carve((size_t)kMaxSlices * 4);
     const size_t o_list = carve((size_t)list_entries((int64_t)H * W) * 4);
     h->dev_bytes = off;
@@ -356,26 +349,18 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     auto up = [&](size_t o, const void *src, size_t bytes) {
         return hipMemcpy(d + o, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
     };
-    bool ok = up(o_px, pkx.data(), pkx.size() * 4) && up(o_py, pky.data(), pky.size() * 4) &&
-              up(o_nx, n2x.data(), n2x.size() * 4) && up(o_ny, n2y.data(), n2y.size() * 4) &&
-              up(o_wt, h->wt.data(), kWKeys * 2) &&
-              up(o_cx, cx.data(), cx.size() * 4) && up(o_cy, cy.data(), cy.size() * 4) &&
+    bool ok = up(o_cx, cx.data(), cx.size() * 4) && up(o_cy, cy.data(), cy.size() * 4) &&
               up(o_pop, pop.data(), pop.size() * 2) &&
               up(o_wpk, wt_pk.data(), wt_pk.size() * 2) &&
               hipMemset(d + o_hrep, 0, 2 * (size_t)kReplicas * nb * 8) == hipSuccess &&
               hipMemset(d + o_hlast, 0, (size_t)nb * 8) == hipSuccess &&
-              hipMemset(d + o_kinfo, 0, 16) == hipSuccess && hipMemset(d + o_count, 0, (size_t)kMaxSlices * 4) == hipSuccess &&
+              hipMemset(d + o_count, 0, (size_t)kMaxSlices * 4) == hipSuccess &&
               hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         (void)hipFree(h->dev);
         delete h;
         return CPE_ERR_HIP;
     }
-    h->tb.pal_x = reinterpret_cast<const int32_t *>(d + o_px);
-    h->tb.pal_y = reinterpret_cast<const int32_t *>(d + o_py);
-    h->tb.n2_x = reinterpret_cast<const uint32_t *>(d + o_nx);
-    h->tb.n2_y = reinterpret_cast<const uint32_t *>(d + o_ny);
-    h->tb.wt = reinterpret_cast<const uint16_t *>(d + o_wt);
     h->tb.cx = reinterpret_cast<const float *>(d + o_cx);
     h->tb.cy = reinterpret_cast<const float *>(d + o_cy);
     h->tb.pop = reinterpret_cast<const uint32_t *>(d + o_pop);
@@ -387,8 +372,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     h->dirty[0] = h->dirty[1] = 0;
     h->sc.dirty = h->dirty;
     h->sc.hlast = reinterpret_cast<unsigned long long *>(d + o_hlast);
-    h->sc.peaks = reinterpret_cast<int32_t *>(d + o_peaks);
-    h->sc.kinfo = reinterpret_cast<int32_t *>(d + o_kinfo);
+    h->sc.plan = reinterpret_cast<BigPlan *>(d + o_plan);
     h->sc.counts = reinterpret_cast<int32_t *>(d + o_count);
     h->sc.list = reinterpret_cast<int32_t *>(d + o_list);
     h->fail_at = -1;

@@ -11,6 +11,8 @@
 
 namespace cpe {
 
+struct BigPlan;     // k_peaks.hpp
+
 // Per-frame scratch of the launch sequence: everything a decode writes and
 // reads besides the caller's inputs and outputs and the handle's constants.
 // The vote histograms come in two sets of set_stride words each.  A frame
@@ -25,8 +27,7 @@ struct Scratch {
     int *parity;                 // host: the set of the next frame (0 or 1)
     size_t *dirty;               // host: [2] leading words of each set that may be nonzero
     unsigned long long *hlast;   // [nb] summed histogram of the frame
-    int32_t *peaks;              // [cap] a | b << 16 (generic path)
-    int32_t *kinfo;              // [0] = min(K, cap), [1] = K (generic path)
+    BigPlan *plan;               // the assignment's plan (grids above 32 x 32)
     int32_t *counts;             // [kMaxSlices] entries per slice of the participating-pixel list
     int32_t *list;               // participating pixels, in slices (list_entries() in cpe_decode.hip)
 };

@@ -768,6 +768,241 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
 // ---------------------------------------------------------------------------
 // Pass 2: assignment + label write-out
 // ---------------------------------------------------------------------------
+// Distances of one tile and up to 32 slots (of which nslot hold candidates)
+// from the accumulators into an array [slot][kKeyStride], scaled by 2^-7 (the
+// root of kScale); dst: this lane's pixel in slot 4 g.
+template <bool EXACT>
+__device__ __forceinline__ void store_distances(const f32x16 &A, const f32x16 &R, int nslot, uint32_t *dst)
+{
+#pragma unroll
+    for (int r4 = 0; r4 < 4; r4++) {
+        if (8 * r4 >= nslot) break;                  // wave-uniform: no candidate in slots 8 r4 ..
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int r = 4 * r4 + i;
+            const float x = assemble(A[r], R[r]);
+            const float d = EXACT ? sqrt_cr(x) : __builtin_amdgcn_sqrtf(x);
+            dst[kKeyStride * (8 * r4 + i)] = __float_as_uint(d);
+        }
+    }
+}
+
+// The candidate batches in LDS (k_peaks.hpp): n of them, padded to a multiple
+// of 8 with batches of the far row, `real` before the padding.
+struct Batches {
+    const u32x4 *bo;
+    const uint32_t *bh, *bk;
+    int n, real;
+};
+
+// Where a tile's results go.  BIG: more candidates than cnt (LDS, kCountCap
+// of them) may exist; the others are counted in their records.
+template <bool BIG>
+struct Labeller {
+    int32_t *labels;
+    float *score_map;
+    double tau32;
+    int32_t *cnt;
+    cpe_centroid *cents;
+
+    __device__ __forceinline__ void label(int pix, int k) const
+    {
+        labels[pix] = k + 1;
+        if (!BIG || k < kCountCap)
+            atomicAdd(cnt + k, 1);
+        else
+            atomicAdd(&cents[k].npix, 1);
+    }
+    // Label and score of pixel `pix`, whose nearest candidate k has the exact
+    // distance sum D (Eq8).
+    __device__ __forceinline__ void put(int pix, int k, double D) const
+    {
+        if (D < tau32) {
+            label(pix, k);
+            if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-5));
+        } else {
+            labels[pix] = 0;
+            if (score_map) score_map[pix] = 0.0f;
+        }
+    }
+};
+
+// Candidate search of one tile from the distance arrays; false, with
+// nothing written, if a pixel is not decided.  Lane l serves the four
+// pixels 4 q .. 4 q + 3 (q = l & 7) over the batches j, j + 8, ... (j =
+// l >> 3): one 16-byte read fetches a column's distances of its four
+// pixels, and the next batch's offsets are read ahead.  Per pixel it keeps
+// the smallest binary32 sum s = fl(min x + y) of a batch and the second
+// smallest, as keys: the bits of s (which order like the sums) with the
+// batch's step in the low `bits` (BITS where it is known: kStepBits).  The first batch only initialises.
+// The eight lanes of a pixel quad then merge in registers (half and row
+// swaps that leave a lane two pixels, one, then a rotation within the row
+// of 16), which leaves pixel m = 4 q + 2 (l >> 5) + (l >> 4 & 1) in lane l
+// and the arrays intact.
+//
+// Let every x and y be within one binary32 step (at most 2^-23 of the
+// value) of the correctly rounded root: the hardware's root is
+// (cpe_check_sqrt verifies sqrt_cr, which only tries it and its two
+// neighbours, on every input).  Then x + y lies within relative 2^-23 of
+// the exact sum, and s within g = 3 2^-24 + 2^-47 of the batch's true
+// minimum D.  If every other batch's s exceeds the winner's s_w by
+// kFastGap steps (each more than 2^-24 s_w), so by more than 2g / (1 - g)
+// s_w, its D is strictly larger (a sum of 0 is exact: any other distance
+// sum is at least 2^-7).  The keys show a gap of s less the step bits.
+// (Merging through LDS, with the batch in a register of its own per pixel
+// and the binary64 sums in the exact kernel, took 43 VALU instructions per
+// step instead of 31 and two LDS round trips more: 1024 x 2048, 16
+// harmonics, fp16, 78.0 against 74.3 us per frame; 2160 x 3840 with 8
+// 239 against 228.)
+// Within the winning batch (one row, one y) a column 3 steps above the
+// smallest is strictly farther.  So a decided pixel has the label of the
+// exact sums.  EXACT (correctly rounded roots): the first column at the
+// batch's smallest x is the nearest, and its D is exact.
+template <bool EXACT, int BITS, bool BIG>
+__device__ __forceinline__ bool search_tile(const Batches &bt, const uint32_t *kx, const uint32_t *ky, int lane, int pix,
+                                            int nvalid, int bits, int force_exact, const Labeller<BIG> &out)
+{
+    const int sh = BITS ? BITS : bits;
+    const uint32_t step_mask = (1u << sh) - 1u;
+    __builtin_amdgcn_wave_barrier();
+    int lo = lane;
+    __asm__ volatile("" : "+v"(lo));        // recomputed per tile, not held across the loop
+    const int q = lo & 7, j0 = lo >> 3;
+    const unsigned char *kxq = reinterpret_cast<const unsigned char *>(kx + 4 * q);
+    const unsigned char *kyq = reinterpret_cast<const unsigned char *>(ky + 4 * q);
+    uint32_t b[4], s2[4];
+    u32x4 o = bt.bo[j0];                     // j0 < 8 <= bt.n
+    uint32_t hb = bt.bh[j0];
+    // the sums of the batch at o, hb; then the offsets of batch `next`
+    // (past the list: bytes of the arrays behind it, never used)
+    auto sums = [&](int next, uint32_t (&sm)[4]) {
+        const u32x4 v0 = *reinterpret_cast<const u32x4 *>(kxq + o.x);
+        const u32x4 v1 = *reinterpret_cast<const u32x4 *>(kxq + o.y);
+        const u32x4 v2 = *reinterpret_cast<const u32x4 *>(kxq + o.z);
+        const u32x4 v3 = *reinterpret_cast<const u32x4 *>(kxq + o.w);
+        const u32x4 yd = *reinterpret_cast<const u32x4 *>(kyq + hb);
+        o = bt.bo[next];
+        hb = bt.bh[next];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const uint32_t m = min(min(v0[e], v1[e]), min(v2[e], v3[e]));
+            sm[e] = __float_as_uint(__uint_as_float(m) + __uint_as_float(yd[e])) & ~step_mask;
+        }
+    };
+    sums(j0 + 8, b);
+#pragma unroll
+    for (int e = 0; e < 4; e++) s2[e] = 0x7f800000u;
+    for (int it = 1; 8 * it < bt.n; it++) {
+        uint32_t sm[4];
+        sums(8 * it + 8 + j0, sm);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const uint32_t key = sm[e] | (uint32_t)it;
+            s2[e] = max(min(b[e], s2[e]), min(max(b[e], s2[e]), key));      // their median
+            b[e] = min(b[e], key);
+        }
+    }
+    // merge (b, s2, lane j) of two parts of one pixel's batches
+    struct Part {
+        uint32_t b, s2, j;
+    };
+    auto merge = [](Part u, Part v) -> Part {
+        Part r;
+        r.j = v.b < u.b ? v.j : u.j;
+        r.s2 = min(min(u.s2, v.s2), max(u.b, v.b));
+        r.b = min(u.b, v.b);
+        return r;
+    };
+    Part p[2];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {           // pixel e in half 0, e + 2 in half 1; j bit 2
+        const u32x2 bb = swap32(b[e], b[e + 2]), ss = swap32(s2[e], s2[e + 2]);
+        p[e] = merge({bb[0], ss[0], (uint32_t)j0 & 3u}, {bb[1], ss[1], (uint32_t)j0 | 4u});
+    }
+    {                                       // pixel + 0 in even rows of 16, + 1 in odd ones; j bit 1
+        const u32x2 bb = swap16(p[0].b, p[1].b), ss = swap16(p[0].s2, p[1].s2), jj = swap16(p[0].j, p[1].j);
+        p[0] = merge({bb[0], ss[0], jj[0]}, {bb[1], ss[1], jj[1]});
+    }
+    p[0] = merge(p[0], {row_ror8(p[0].b), row_ror8(p[0].s2), row_ror8(p[0].j)});   // j bit 0
+    const int m = 4 * q + 2 * (lo >> 5) + ((lo >> 4) & 1);
+    const int pm = __shfl(pix, m);
+    const int bi = (int)(8u * (p[0].b & step_mask) + p[0].j);
+    const u32x4 ow = bt.bo[bi];
+    const int k0 = (int)bt.bk[bi];
+    const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + m);
+    const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + ow.x);
+    const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + ow.y);
+    const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + ow.z);
+    const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + ow.w);
+    const uint32_t l01 = min(w0, w1), l23 = min(w2, w3), wm = min(l01, l23);
+    const int k = k0 + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
+    bool amb = (p[0].s2 >> sh) - (p[0].b >> sh) < (kFastGap + 2u * step_mask) >> sh;
+    if constexpr (!EXACT) {
+        const uint32_t second = min(min(max(w0, w1), max(w2, w3)), max(l01, l23));
+        amb |= second - wm < 3u;
+    }
+    // one of the two lanes that hold the pixel
+    const bool valid = (lo & 8) == 0 && m < nvalid;
+    if (force_exact || __ballot(amb && valid)) return false;
+    if (valid) {
+        if constexpr (EXACT) {
+            const uint32_t y = *reinterpret_cast<const uint32_t *>(
+                reinterpret_cast<const unsigned char *>(ky + m) + bt.bh[bi]);
+            const double D = (double)__uint_as_float(wm) + (double)__uint_as_float(y);
+            out.put(pm, k, D);
+        } else {
+            out.label(pm, k);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    return true;
+}
+
+// The tiles that the search leaves undecided, from exact distances: lane
+// m (either half: half g takes the batches g, g + 2, ...) scans every
+// batch for pixel m.  The smallest x distance of a batch plus the row's y
+// distance, summed exactly in binary64, has at least 12 zero bits at the
+// bottom of its mantissa (both distances are 0 or binary32 values of at
+// least 2^-7, so the sum is a multiple of 2^-30 below 2^10), which take the
+// batch index (at most INDEX < 4096): one binary64 minimum selects the smallest sum and,
+// on ties, the first batch, and its first column at the batch's minimum
+// is the lowest candidate index.
+template <uint32_t INDEX, bool BIG>
+__device__ __forceinline__ void search_exact(const Batches &bt, const uint32_t *kx, const uint32_t *ky, int lane,
+                                             int pix, int nvalid, const Labeller<BIG> &out)
+{
+    const int g = lane >> 5, ln = lane & 31;
+    __builtin_amdgcn_wave_barrier();
+    const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + ln);
+    const unsigned char *kyl = reinterpret_cast<const unsigned char *>(ky + ln);
+    double best = __builtin_inf();
+    for (int bi = g; bi < bt.real; bi += 2) {
+        const u32x4 o = bt.bo[bi];
+        const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + o.x);
+        const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + o.y);
+        const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + o.z);
+        const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + o.w);
+        const uint32_t yv = *reinterpret_cast<const uint32_t *>(kyl + bt.bh[bi]);
+        const uint32_t m = min(min(w0, w1), min(w2, w3));
+        const double sum = (double)__uint_as_float(m) + (double)__uint_as_float(yv);
+        const unsigned long long sb = (unsigned long long)__double_as_longlong(sum);
+        best = min_f64(best, __longlong_as_double((long long)((sb & ~0xffffffffull) | ((uint32_t)sb | (uint32_t)bi))));
+    }
+    best = min_f64(best, __shfl_xor(best, 32));
+    const unsigned long long key = (unsigned long long)__double_as_longlong(best);
+    const int bi = (int)((uint32_t)key & INDEX);
+    const u32x4 o = bt.bo[bi];
+    const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + o.x);
+    const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + o.y);
+    const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + o.z);
+    const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + o.w);
+    const uint32_t wm = min(min(w0, w1), min(w2, w3));
+    if (g == 0 && ln < nvalid)
+        out.put(pix, (int)bt.bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3),
+            __longlong_as_double((long long)(key & ~(unsigned long long)INDEX)));
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Waves per SIMD of the assignment kernel: four where the register
 // allocation fits 128 registers without spilling (vector input slices and up
 // to 9 harmonics, or fp16 with 16), three otherwise; one workgroup per
@@ -958,205 +1193,12 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
                 pop[k] = kPalRegs ? popr[ax][k] : palette_operand<F>(s_pop, ax, k, slotbin[ax]);
             f32x16 A, R;
             axis_products<T, F, false>(X.ax[ax], X.e, pop, A, R);
-            uint32_t *dst = (ax ? ky : kx) + 4 * g * kKeyStride + ln;
-#pragma unroll
-            for (int r4 = 0; r4 < 4; r4++) {
-                if (8 * r4 >= nslot[ax]) break;      // wave-uniform: no candidate in slots 8 r4 ..
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int r = 4 * r4 + i;
-                    const float x = assemble(A[r], R[r]);
-                    const float d = decltype(exact)::value ? sqrt_cr(x) : __builtin_amdgcn_sqrtf(x);
-                    dst[kKeyStride * (8 * r4 + i)] = __float_as_uint(d);
-                }
-            }
+            store_distances<decltype(exact)::value>(A, R, nslot[ax], (ax ? ky : kx) + 4 * g * kKeyStride + ln);
         }
     };
 
-    // Label and score of pixel `pix`, whose nearest candidate k has the exact
-    // distance sum D (Eq8).
-    auto put = [&](int pix, int k, double D) {
-        if (D < tau32) {
-            labels[pix] = k + 1;
-            if (score_map) score_map[pix] = expf(-(float)(D * 0x1p-5));
-            atomicAdd(s_cnt + k, 1);
-        } else {
-            labels[pix] = 0;
-            if (score_map) score_map[pix] = 0.0f;
-        }
-    };
-
-    // Candidate search of one tile from the distance arrays; false, with
-    // nothing written, if a pixel is not decided.  Lane l serves the four
-    // pixels 4 q .. 4 q + 3 (q = l & 7) over the batches j, j + 8, ... (j =
-    // l >> 3): one 16-byte read fetches a column's distances of its four
-    // pixels, and the next batch's offsets are read ahead.  Per pixel it keeps
-    // the smallest binary32 sum s = fl(min x + y) of a batch and the second
-    // smallest, as keys: the bits of s (which order like the sums) with the
-    // batch's step in the low kStepBits.  The first batch only initialises.
-    // The eight lanes of a pixel quad then merge in registers (half and row
-    // swaps that leave a lane two pixels, one, then a rotation within the row
-    // of 16), which leaves pixel m = 4 q + 2 (l >> 5) + (l >> 4 & 1) in lane l
-    // and the arrays intact.
-    //
-    // Let every x and y be within one binary32 step (at most 2^-23 of the
-    // value) of the correctly rounded root: the hardware's root is
-    // (cpe_check_sqrt verifies sqrt_cr, which only tries it and its two
-    // neighbours, on every input).  Then x + y lies within relative 2^-23 of
-    // the exact sum, and s within g = 3 2^-24 + 2^-47 of the batch's true
-    // minimum D.  If every other batch's s exceeds the winner's s_w by
-    // kFastGap steps (each more than 2^-24 s_w), so by more than 2g / (1 - g)
-    // s_w, its D is strictly larger (a sum of 0 is exact: any other distance
-    // sum is at least 2^-7).  The keys show a gap of s less the step bits.
-    // (Merging through LDS, with the batch in a register of its own per pixel
-    // and the binary64 sums in the exact kernel, took 43 VALU instructions per
-    // step instead of 31 and two LDS round trips more: 1024 x 2048, 16
-    // harmonics, fp16, 78.0 against 74.3 us per frame; 2160 x 3840 with 8
-    // 239 against 228.)
-    // Within the winning batch (one row, one y) a column 3 steps above the
-    // smallest is strictly farther.  So a decided pixel has the label of the
-    // exact sums.  EXACT (correctly rounded roots): the first column at the
-    // batch's smallest x is the nearest, and its D is exact.
-    auto search = [&](auto exact, int pix, int nvalid) -> bool {
-        constexpr bool kExact = decltype(exact)::value;
-        constexpr uint32_t kStepMask = (1u << kStepBits) - 1u;
-        __builtin_amdgcn_wave_barrier();
-        int lo = lane;
-        __asm__ volatile("" : "+v"(lo));        // recomputed per tile, not held across the loop
-        const int q = lo & 7, j0 = lo >> 3;
-        const unsigned char *kxq = reinterpret_cast<const unsigned char *>(kx + 4 * q);
-        const unsigned char *kyq = reinterpret_cast<const unsigned char *>(ky + 4 * q);
-        uint32_t b[4], s2[4];
-        u32x4 o = s_bo[j0];                     // j0 < 8 <= nbat
-        uint32_t hb = s_bh[j0];
-        // the sums of the batch at o, hb; then the offsets of batch `next`
-        // (past the list: bytes of the arrays behind it, never used)
-        auto sums = [&](int next, uint32_t (&sm)[4]) {
-            const u32x4 v0 = *reinterpret_cast<const u32x4 *>(kxq + o.x);
-            const u32x4 v1 = *reinterpret_cast<const u32x4 *>(kxq + o.y);
-            const u32x4 v2 = *reinterpret_cast<const u32x4 *>(kxq + o.z);
-            const u32x4 v3 = *reinterpret_cast<const u32x4 *>(kxq + o.w);
-            const u32x4 yd = *reinterpret_cast<const u32x4 *>(kyq + hb);
-            o = s_bo[next];
-            hb = s_bh[next];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const uint32_t m = min(min(v0[e], v1[e]), min(v2[e], v3[e]));
-                sm[e] = __float_as_uint(__uint_as_float(m) + __uint_as_float(yd[e])) & ~kStepMask;
-            }
-        };
-        sums(j0 + 8, b);
-#pragma unroll
-        for (int e = 0; e < 4; e++) s2[e] = 0x7f800000u;
-        for (int it = 1; 8 * it < nbat; it++) {
-            uint32_t sm[4];
-            sums(8 * it + 8 + j0, sm);
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const uint32_t key = sm[e] | (uint32_t)it;
-                s2[e] = max(min(b[e], s2[e]), min(max(b[e], s2[e]), key));      // their median
-                b[e] = min(b[e], key);
-            }
-        }
-        // merge (b, s2, lane j) of two parts of one pixel's batches
-        struct Part {
-            uint32_t b, s2, j;
-        };
-        auto merge = [](Part u, Part v) -> Part {
-            Part r;
-            r.j = v.b < u.b ? v.j : u.j;
-            r.s2 = min(min(u.s2, v.s2), max(u.b, v.b));
-            r.b = min(u.b, v.b);
-            return r;
-        };
-        Part p[2];
-#pragma unroll
-        for (int e = 0; e < 2; e++) {           // pixel e in half 0, e + 2 in half 1; j bit 2
-            const u32x2 bb = swap32(b[e], b[e + 2]), ss = swap32(s2[e], s2[e + 2]);
-            p[e] = merge({bb[0], ss[0], (uint32_t)j0 & 3u}, {bb[1], ss[1], (uint32_t)j0 | 4u});
-        }
-        {                                       // pixel + 0 in even rows of 16, + 1 in odd ones; j bit 1
-            const u32x2 bb = swap16(p[0].b, p[1].b), ss = swap16(p[0].s2, p[1].s2), jj = swap16(p[0].j, p[1].j);
-            p[0] = merge({bb[0], ss[0], jj[0]}, {bb[1], ss[1], jj[1]});
-        }
-        p[0] = merge(p[0], {row_ror8(p[0].b), row_ror8(p[0].s2), row_ror8(p[0].j)});   // j bit 0
-        const int m = 4 * q + 2 * (lo >> 5) + ((lo >> 4) & 1);
-        const int pm = __shfl(pix, m);
-        const int bi = (int)(8u * (p[0].b & kStepMask) + p[0].j);
-        const u32x4 ow = s_bo[bi];
-        const int k0 = (int)s_bk[bi];
-        const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + m);
-        const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + ow.x);
-        const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + ow.y);
-        const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + ow.z);
-        const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + ow.w);
-        const uint32_t l01 = min(w0, w1), l23 = min(w2, w3), wm = min(l01, l23);
-        const int k = k0 + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
-        bool amb = (p[0].s2 >> kStepBits) - (p[0].b >> kStepBits) <
-                   (uint32_t)(kFastGap + 2 * (int)kStepMask) >> kStepBits;
-        if constexpr (!kExact) {
-            const uint32_t second = min(min(max(w0, w1), max(w2, w3)), max(l01, l23));
-            amb |= second - wm < 3u;
-        }
-        // one of the two lanes that hold the pixel
-        const bool valid = (lo & 8) == 0 && m < nvalid;
-        if (force_exact || __ballot(amb && valid)) return false;
-        if (valid) {
-            if constexpr (kExact) {
-                const uint32_t y = *reinterpret_cast<const uint32_t *>(
-                    reinterpret_cast<const unsigned char *>(ky + m) + s_bh[bi]);
-                const double D = (double)__uint_as_float(wm) + (double)__uint_as_float(y);
-                put(pm, k, D);
-            } else {
-                labels[pm] = k + 1;
-                atomicAdd(s_cnt + k, 1);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        return true;
-    };
-
-    // The tiles that the search leaves undecided, from exact distances: lane
-    // m (either half: half g takes the batches g, g + 2, ...) scans every
-    // batch for pixel m.  The smallest x distance of a batch plus the row's y
-    // distance, summed exactly in binary64, has at least 12 zero bits at the
-    // bottom of its mantissa (both distances are 0 or binary32 values of at
-    // least 2^-7, so the sum is a multiple of 2^-30 below 2^10), which take the
-    // batch index (< 128): one binary64 minimum selects the smallest sum and,
-    // on ties, the first batch, and its first column at the batch's minimum
-    // is the lowest candidate index.
-    const int nbr = min(pl.nbat_real, kMaxBatchLds);
-    auto search_pix = [&](int pix, int nvalid) {
-        __builtin_amdgcn_wave_barrier();
-        const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + ln);
-        const unsigned char *kyl = reinterpret_cast<const unsigned char *>(ky + ln);
-        double best = __builtin_inf();
-        for (int bi = g; bi < nbr; bi += 2) {
-            const u32x4 o = s_bo[bi];
-            const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + o.x);
-            const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + o.y);
-            const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + o.z);
-            const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + o.w);
-            const uint32_t yv = *reinterpret_cast<const uint32_t *>(kyl + s_bh[bi]);
-            const uint32_t m = min(min(w0, w1), min(w2, w3));
-            const double sum = (double)__uint_as_float(m) + (double)__uint_as_float(yv);
-            const unsigned long long sb = (unsigned long long)__double_as_longlong(sum);
-            best = min_f64(best, __longlong_as_double((long long)((sb & ~0xffffffffull) | ((uint32_t)sb | (uint32_t)bi))));
-        }
-        best = min_f64(best, __shfl_xor(best, 32));
-        const unsigned long long key = (unsigned long long)__double_as_longlong(best);
-        const int bi = (int)((uint32_t)key & 127u);
-        const u32x4 o = s_bo[bi];
-        const uint32_t w0 = *reinterpret_cast<const uint32_t *>(kxl + o.x);
-        const uint32_t w1 = *reinterpret_cast<const uint32_t *>(kxl + o.y);
-        const uint32_t w2 = *reinterpret_cast<const uint32_t *>(kxl + o.z);
-        const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + o.w);
-        const uint32_t wm = min(min(w0, w1), min(w2, w3));
-        if (g == 0 && ln < nvalid)
-            put(pix, (int)s_bk[bi] + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3),
-                __longlong_as_double((long long)(key & ~127ull)));
-        __builtin_amdgcn_wave_barrier();
-    };
+    const Batches bt{s_bo, s_bh, s_bk, nbat, min(pl.nbat_real, kMaxBatchLds)};
+    const Labeller<false> out{labels, score_map, tau32, s_cnt, nullptr};
 
     // the next tile's rows are loaded as soon as the current ones are converted
     int tn = tend, ipn = 0;                             // next tile; this lane's pixel in it
@@ -1176,15 +1218,16 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const int nvalid = min(32, n - 32 * t);
         if constexpr (FAST) {
             distances(std::false_type{}, raw, next);
-            if (!search(std::false_type{}, ip, nvalid)) {
+            if (!search_tile<false, kStepBits>(bt, kx, ky, lane, ip, nvalid, kStepBits, force_exact, out)) {
                 raw.load(emb + (size_t)ip * dstride, yoff, g);          // this tile's rows again
                 distances(std::true_type{}, raw, []() {});
                 if (tn < tend) raw.load(emb + (size_t)ipn * dstride, yoff, g);   // the next tile's rows again
-                search_pix(ip, nvalid);
+                search_exact<127>(bt, kx, ky, lane, ip, nvalid, out);
             }
         } else {
             distances(std::true_type{}, raw, next);
-            if (!search(std::true_type{}, ip, nvalid)) search_pix(ip, nvalid);
+            if (!search_tile<true, kStepBits>(bt, kx, ky, lane, ip, nvalid, kStepBits, force_exact, out))
+                search_exact<127>(bt, kx, ky, lane, ip, nvalid, out);
         }
         t = tn;
         tn = tnn;

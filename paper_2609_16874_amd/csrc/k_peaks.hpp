@@ -9,9 +9,9 @@
 //                 matrix-core assignment kernel in its prologue, entirely in
 //                 LDS, as candidate masks of the rows and the candidate
 //                 batches of the assignment search.
-//   peak_extract  any grid: the stand-alone kernel k_peaks between the
-//                 generic vote and assignment kernels; it writes the records,
-//                 K, the compact list and the summed histogram to memory.
+//   k_peaks       larger grids: a stand-alone kernel between the vote and
+//                 the assignment kernels; it writes the records, K, the
+//                 summed histogram and the assignment's plan to memory.
 //
 // Candidate batches.  The first min(K, cap) candidates are grouped by row b
 // into batches of 4 columns (a row's last batch is filled with the far row,
@@ -22,6 +22,8 @@
 // batches of the far row.
 #pragma once
 
+#include <type_traits>
+
 #include "cpe_common.hpp"
 
 namespace cpe {
@@ -31,83 +33,6 @@ typedef uint32_t u32x4_pk __attribute__((ext_vector_type(4)));
 // Strict local maxima of a B_w x B_h grid are pairwise non-adjacent, so there
 // are at most ceil(B_w / 2) * ceil(B_h / 2) of them.
 __host__ __device__ constexpr int max_peaks(int Bw, int Bh) { return ((Bw + 1) / 2) * ((Bh + 1) / 2); }
-
-// Strict 8-neighbour local maximum of s_h (LDS, row-major [Bh][Bw]) above
-// `cut`; out-of-range neighbours are ignored.
-__device__ __forceinline__ bool is_peak(const unsigned long long *s_h, int i, int Bw, int Bh, long long cut)
-{
-    const int a = i % Bw, b = i / Bw;
-    const unsigned long long v = s_h[i];
-    bool f = (long long)v > cut;
-#pragma unroll
-    for (int db = -1; db <= 1; db++)
-#pragma unroll
-        for (int da = -1; da <= 1; da++) {
-            if (!da && !db) continue;
-            const int nb_ = b + db, na = a + da;
-            const bool in = nb_ >= 0 && nb_ < Bh && na >= 0 && na < Bw;
-            const unsigned long long w = s_h[in ? nb_ * Bw + na : i];   // self when out of range
-            f = f && (!in || v > w);
-        }
-    return f;
-}
-
-// Block-level scratch of the compaction (LDS).
-struct CompactScratch {
-    int wave[32];                 // per-wave counts of the two bins per thread
-    int base;
-};
-
-// Mark and compact the candidates of s_h in ascending bin order into s_pk;
-// returns K (every thread).  Two bins per thread and pass, bins
-// c0 + u * blockDim + tid.  on_peak(i, pos) runs for every candidate bin i
-// at list position pos.
-template <typename OnPeak>
-__device__ __forceinline__ int compact_peaks(const unsigned long long *s_h, int Bw, int Bh, long long cut, int *s_pk,
-                                             CompactScratch &cs, OnPeak on_peak)
-{
-    const int tid = threadIdx.x, nb = Bw * Bh;
-    const int lane = tid & 63, wid = tid >> 6, nwaves = blockDim.x >> 6;
-    if (tid == 0) cs.base = 0;
-    __syncthreads();
-    for (int c0 = 0; c0 < nb; c0 += 2 * (int)blockDim.x) {
-        bool flag[2];
-        unsigned long long mask[2];
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            const int i = c0 + u * (int)blockDim.x + tid;
-            flag[u] = i < nb && is_peak(s_h, i, Bw, Bh, cut);
-            mask[u] = __ballot(flag[u]);
-        }
-        if (lane == 0) {
-            cs.wave[wid] = __popcll(mask[0]);
-            cs.wave[nwaves + wid] = __popcll(mask[1]);
-        }
-        __syncthreads();
-        // all counts of this pass: pass 0 of every wave, then pass 1
-        int off0 = cs.base, off1 = cs.base, tot = 0;
-#pragma unroll
-        for (int w = 0; w < 16; w++) {          // nwaves <= 16; all reads independent
-            const int n0 = w < nwaves ? cs.wave[w] : 0, n1 = w < nwaves ? cs.wave[nwaves + w] : 0;
-            off0 += w < wid ? n0 : 0;
-            off1 += n0 + (w < wid ? n1 : 0);
-            tot += n0 + n1;
-        }
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            if (flag[u]) {
-                const int i = c0 + u * (int)blockDim.x + tid;
-                const int pos = (u ? off1 : off0) + lane_prefix(mask[u]);   // < max_peaks(Bw, Bh)
-                s_pk[pos] = i;
-                on_peak(i, pos);
-            }
-        }
-        __syncthreads();
-        if (tid == 0) cs.base += tot;
-        __syncthreads();
-    }
-    return cs.base;
-}
 
 // ---------------------------------------------------------------------------
 // Grids up to 32 x 32: candidates in LDS, in the assignment kernel's prologue
@@ -281,73 +206,218 @@ __device__ __forceinline__ void peaks_lds_find(const PeakBins<WAVES> &pb, long l
 }
 
 // ---------------------------------------------------------------------------
-// Any grid: the stand-alone peak kernel of the generic path
+// Grids above 32 x 32: the stand-alone peak kernel
 // ---------------------------------------------------------------------------
-struct PeakOut {
-    cpe_centroid *cents;          // caller's centroid records [cap]
-    int32_t *num;                 // caller's K
-    int32_t *peaks;               // [cap] a | b << 16
-    int32_t *kinfo;               // [0] = min(K, cap), [1] = K
+// What the assignment needs of the candidates, in global memory: this header,
+// then the batches' column offsets (16 bytes each), row offsets and first
+// candidates (4 bytes each), arrays of max_batches() + kBatchPad entries.
+struct BigPlan {
+    int32_t K, Kc;                // candidates; min(K, cap)
+    int32_t nbat, nbat_real;      // batches with and without the padding
+    int32_t ncol, nrow;           // candidate columns and rows
+    int32_t reserved[2];
+    uint8_t colbin[kMaxBins], rowbin[kMaxBins];   // bins of the column and row slots (ascending)
 };
+static_assert(sizeof(BigPlan) % 16 == 0, "the batch offsets follow, 16-byte aligned");
 
-// The whole extraction; every thread of the block calls it.  s_h: LDS
-// scratch of Bw * Bh u64; s_pk: LDS scratch of max_peaks(Bw, Bh) ints.
-// Until the last barrier every result goes to LDS only, so that no barrier
-// waits for global stores; the outputs are written at the end.
-__device__ __forceinline__ void peak_extract(const unsigned long long *__restrict__ hrep,
-                                             unsigned long long *__restrict__ hlast, int32_t Bw, int32_t Bh,
-                                             long long cut, int32_t cap, const float *__restrict__ cx,
-                                             const float *__restrict__ cy, const PeakOut &po,
-                                             unsigned long long *s_h, int *s_pk, CompactScratch &cs)
+// Upper bound of the batches of a grid: strict maxima are never horizontally
+// adjacent, so a row holds at most ceil(B_w / 2).
+__host__ __device__ constexpr int max_batches(int Bw, int Bh) { return Bh * (((Bw + 1) / 2 + 3) / 4); }
+__host__ __device__ constexpr size_t plan_bytes(int Bw, int Bh)
 {
-    const int tid = threadIdx.x;
-    const int nb = Bw * Bh;
-    for (int i = tid; i < nb; i += blockDim.x) {
-        unsigned long long v[kReplicas];
-#pragma unroll
-        for (int r = 0; r < kReplicas; r++) v[r] = hrep[(size_t)r * nb + i];
-        unsigned long long sum = 0;
-#pragma unroll
-        for (int r = 0; r < kReplicas; r++) sum += v[r];
-        s_h[i] = sum;
-    }
-    const int K = compact_peaks(s_h, Bw, Bh, cut, s_pk, cs, [](int, int) {});
-    const int Kc = K < cap ? K : cap;
-
-    // ---- outputs (global stores only from here on) ----
-    for (int k = tid; k < Kc; k += blockDim.x) {
-        const int i = s_pk[k], a = i % Bw, b = i / Bw;
-        cpe_centroid rec;
-        rec.bin_x = a;
-        rec.bin_y = b;
-        rec.x = cx[a];
-        rec.y = cy[b];
-        rec.score = (double)s_h[i] * 0x1p-30;
-        rec.npix = 0;
-        rec.reserved = 0;
-        po.cents[k] = rec;
-        po.peaks[k] = a | (b << 16);
-    }
-    for (int i = tid; i < nb; i += blockDim.x) hlast[i] = s_h[i];
-    if (tid == 0) {
-        *po.num = K;
-        po.kinfo[0] = Kc;
-        po.kinfo[1] = K;
-    }
+    return sizeof(BigPlan) + 24 * (size_t)(max_batches(Bw, Bh) + kBatchPad);
+}
+template <typename P>      // BigPlan, const or not
+__device__ __forceinline__ auto plan_offsets(P *p)
+{
+    using V = std::conditional_t<std::is_const_v<P>, const u32x4_pk, u32x4_pk>;
+    return reinterpret_cast<V *>(p + 1);
+}
+template <typename P>
+__device__ __forceinline__ auto plan_rows(P *p, int max_bat)
+{
+    using V = std::conditional_t<std::is_const_v<P>, const uint32_t, uint32_t>;
+    return reinterpret_cast<V *>(plan_offsets(p) + max_bat + kBatchPad);
+}
+template <typename P>
+__device__ __forceinline__ auto plan_first(P *p, int max_bat)
+{
+    return plan_rows(p, max_bat) + max_bat + kBatchPad;
 }
 
 namespace {   // one private copy per translation unit that launches it
 
+// One workgroup: sums the vote histograms into LDS (rows of B_w + 2 counts
+// with a border of -1), tests the bins for candidates (a wave takes 64 columns
+// of a row at a time, whose ballot is a word of the row's mask), builds the
+// plan from the row masks (one wave, two rows per lane) and writes the
+// centroid records, K and the summed histogram.  The launch is a chain of
+// latencies: its loads are issued kUnroll bins at a time, and everything after
+// the masks is local to a lane's rows.
 __global__ __launch_bounds__(1024) void k_peaks(const unsigned long long *__restrict__ hrep,
                                                 unsigned long long *__restrict__ hlast, int32_t Bw, int32_t Bh,
                                                 long long cut, int32_t cap, const float *__restrict__ cx,
-                                                const float *__restrict__ cy, PeakOut po)
+                                                const float *__restrict__ cy, cpe_centroid *__restrict__ cents,
+                                                int32_t *__restrict__ num, BigPlan *__restrict__ plan,
+                                                int32_t max_bat)
 {
+    constexpr int kUnroll = 4;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ CompactScratch cs;
-    unsigned long long *s_h = reinterpret_cast<unsigned long long *>(smem);    // [Bw * Bh]
-    int *s_pk = reinterpret_cast<int *>(s_h + Bw * Bh);                          // [max_peaks(Bw, Bh)]
-    peak_extract(hrep, hlast, Bw, Bh, cut, cap, cx, cy, po, s_h, s_pk, cs);
+    long long *s_h = reinterpret_cast<long long *>(smem);                     // [Bh + 2][Bw + 2]
+    __shared__ unsigned long long s_mask[kMaxBins][2];                        // candidate columns of a row
+    __shared__ int s_first[kMaxBins];                                         // its first candidate
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nb = Bw * Bh, stride = Bw + 2;
+    const int csh = Bw > 64 ? 1 : 0, words = Bh << csh;                       // 64-column words of the rows
+    // word i: row i >> csh, columns 64 (i & csh) ..
+    auto bin = [&](int i, int &a, int &b) {
+        b = i >> csh;
+        a = 64 * (i & csh) + lane;
+        return i < words && a < Bw;
+    };
+    for (int w0 = wv; w0 < words; w0 += 16 * kUnroll) {
+        unsigned long long v[kUnroll][kReplicas];
+#pragma unroll
+        for (int u = 0; u < kUnroll; u++) {
+            int a, b;
+            const bool in = bin(w0 + 16 * u, a, b);
+#pragma unroll
+            for (int r = 0; r < kReplicas; r++) v[u][r] = in ? hrep[(size_t)r * nb + b * Bw + a] : 0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; u++) {
+            int a, b;
+            if (!bin(w0 + 16 * u, a, b)) continue;
+            unsigned long long sum = 0;
+#pragma unroll
+            for (int r = 0; r < kReplicas; r++) sum += v[u][r];
+            s_h[(b + 1) * stride + a + 1] = (long long)sum;
+        }
+    }
+    for (int i = tid; i < 2 * stride + 2 * Bh; i += 1024) {
+        const int j = i - 2 * stride;
+        s_h[i < stride ? i : j < 0 ? (Bh + 1) * stride + i - stride : (j / 2 + 1) * stride + (j & 1) * (Bw + 1)] = -1;
+    }
+    if (tid < 2 * kMaxBins) s_mask[tid >> 1][tid & 1] = 0ull;
+    __syncthreads();
+    for (int i = wv; i < words; i += 16) {
+        int a, b;
+        bool f = bin(i, a, b);
+        const long long *q = s_h + b * stride + (f ? a : 0);                  // the corner of its neighbourhood
+        const long long v = q[stride + 1];
+        f = f && v > cut;
+#pragma unroll
+        for (int n = 0; n < 9; n++)
+            if (n != 4) f &= v > q[(n / 3) * stride + n % 3];
+        const unsigned long long m = __ballot(f);
+        if (lane == 0) s_mask[b][i & csh] = m;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // rows 2 lane and 2 lane + 1; c: candidates, cut off at `cap`
+        unsigned long long m[2][2];
+        int c[2], first[2], nbt[2];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            m[u][0] = s_mask[2 * lane + u][0];
+            m[u][1] = s_mask[2 * lane + u][1];
+            c[u] = __popcll(m[u][0]) + __popcll(m[u][1]);
+        }
+        const int upto = wave_incl_sum(c[0] + c[1]), K = __builtin_amdgcn_readlane(upto, 63);
+        first[0] = upto - c[0] - c[1];
+        first[1] = upto - c[1];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            int over = min(max(first[u] + c[u] - cap, 0), c[u]);
+            c[u] -= over;
+            for (; over > 0; over--) {
+                const int w = m[u][1] ? 1 : 0;
+                m[u][w] &= ~(1ull << (63 - __clzll(m[u][w])));
+            }
+            nbt[u] = (c[u] + 3) >> 2;
+            s_mask[2 * lane + u][0] = m[u][0];
+            s_mask[2 * lane + u][1] = m[u][1];
+            s_first[2 * lane + u] = first[u];
+        }
+        // the candidate columns
+        unsigned long long cm[2];
+#pragma unroll
+        for (int w = 0; w < 2; w++) {
+            const unsigned long long x = m[0][w] | m[1][w];
+            cm[w] = (unsigned long long)wave_or64((uint32_t)x) | (unsigned long long)wave_or64((uint32_t)(x >> 32)) << 32;
+        }
+        auto col_slot = [&](int a) {
+            const unsigned long long below = (1ull << (a & 63)) - 1ull;
+            return a < 64 ? __popcll(cm[0] & below) : __popcll(cm[0]) + __popcll(cm[1] & below);
+        };
+        const int ncol = __popcll(cm[0]) + __popcll(cm[1]);
+        const unsigned long long r0 = __ballot(c[0] > 0), r1 = __ballot(c[1] > 0);
+        const int nrow = __popcll(r0) + __popcll(r1);
+        const int slot0 = lane_prefix(r0) + lane_prefix(r1);                   // row slot of row 2 lane
+        const uint32_t far_y = 4u * kKeyStride * (uint32_t)((nrow + 7) & ~7);
+        const uint32_t far_x = far_y + 4u * kKeyStride * (uint32_t)((ncol + 7) & ~7);
+#pragma unroll
+        for (int w = 0; w < 2; w++) {
+            const int a = 64 * w + lane;
+            if ((cm[w] >> lane) & 1ull) plan->colbin[col_slot(a)] = (uint8_t)a;
+        }
+        const int incl = wave_incl_sum(nbt[0] + nbt[1]);
+        const int total = __builtin_amdgcn_readlane(incl, 63), padded = (total + kBatchPad - 1) & ~(kBatchPad - 1);
+        u32x4_pk *bo = plan_offsets(plan);
+        uint32_t *bh = plan_rows(plan, max_bat), *bk = plan_first(plan, max_bat);
+        int at = incl - nbt[0] - nbt[1];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const int slot = slot0 + (u && c[0] > 0 ? 1 : 0);
+            if (c[u] > 0) plan->rowbin[slot] = (uint8_t)(2 * lane + u);
+            for (int j = 0; j < nbt[u]; j++, at++) {
+                u32x4_pk o;
+#pragma unroll
+                for (int s4 = 0; s4 < 4; s4++) {
+                    o[s4] = far_x;
+                    const int w = m[u][0] ? 0 : 1;
+                    if (m[u][w]) {
+                        o[s4] = 4u * kKeyStride * (uint32_t)col_slot(64 * w + __builtin_ctzll(m[u][w]));
+                        m[u][w] &= m[u][w] - 1ull;
+                    }
+                }
+                bo[at] = o;
+                bh[at] = 4u * kKeyStride * (uint32_t)slot;
+                bk[at] = (uint32_t)(first[u] + 4 * j);
+            }
+        }
+        if (lane < padded - total) {
+            bo[total + lane] = u32x4_pk{far_x, far_x, far_x, far_x};
+            bh[total + lane] = far_y;
+            bk[total + lane] = 0u;
+        }
+        if (lane == 0) {
+            plan->K = *num = K;
+            plan->Kc = min(K, cap);
+            plan->nbat = padded;
+            plan->nbat_real = total;
+            plan->ncol = ncol;
+            plan->nrow = nrow;
+        }
+    }
+    __syncthreads();
+    for (int i = wv; i < words; i += 16) {
+        int a, b;
+        if (!bin(i, a, b)) continue;
+        const long long v = s_h[(b + 1) * stride + a + 1];
+        hlast[b * Bw + a] = (unsigned long long)v;
+        const unsigned long long m = s_mask[b][i & csh];
+        if ((m >> lane) & 1ull) {
+            cpe_centroid rec;
+            rec.bin_x = a;
+            rec.bin_y = b;
+            rec.x = cx[a];
+            rec.y = cy[b];
+            rec.score = (double)v * 0x1p-30;
+            rec.npix = 0;
+            rec.reserved = 0;
+            cents[s_first[b] + __popcll(m & ((1ull << lane) - 1ull)) + (i & csh ? __popcll(s_mask[b][0]) : 0)] = rec;
+        }
+    }
 }
 
 }  // namespace

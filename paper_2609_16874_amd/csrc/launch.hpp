@@ -6,7 +6,7 @@
 
 #include "cpe_decoder.hpp"
 #include "k_compact.hpp"
-#include "k_generic.hpp"
+#include "k_assign_big.hpp"
 #include "k_mfma.hpp"
 #include "k_peaks.hpp"
 
@@ -27,14 +27,6 @@ constexpr int64_t kAssignGrid = 256;
 // (640 x 640: 36.4, 39.4) and keep the exact one.
 template <typename T, int F>
 constexpr int64_t kFastSearchPixels = F <= 8 ? 1LL << 18 : sizeof(T) == 2 ? 1LL << 19 : INT64_MAX;
-
-// Largest pixel tile (threads per block) whose LDS footprint fits the budget.
-inline int pick_tile(size_t fixed, size_t per_px, size_t budget)
-{
-    for (int tp = 256; tp >= 64; tp >>= 1)
-        if (fixed + per_px * (size_t)tp <= budget) return tp;
-    return 64;
-}
 
 template <typename T, int F>
 cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
@@ -140,53 +132,50 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
                     FusedArgs{}))
             return CPE_ERR_HIP;
     }
+    // labels only (no score map, no Eq8 threshold): the fast search may serve
+    const bool labels_only = score == nullptr && !(fa.tau4096 < __builtin_inf());
+    const double tau32 = fa.tau4096 * 0x1p-7;
+    const int32_t force_exact = h->search_mode == 1;
     if (mfma) {
         // launch 2: peak extraction in every workgroup's prologue, assignment
         constexpr int wpb2 = kAssignWpb<T, F>;
         const int64_t wgs2 = (tiles + wpb2 - 1) / wpb2;
         const int grid2 = (int)(wgs2 < kAssignGrid ? wgs2 : kAssignGrid);
-        // labels only (no score map, no Eq8 threshold) on large frames: the
-        // fast search, which pays off when every wave has several tiles (it
-        // shortens each tile's work but lengthens its dependency chain)
-        const bool labels_only = score == nullptr && !(fa.tau4096 < __builtin_inf());
         const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels<T, F>);
         auto assign_kernel = fast ? k_assign_mfma<T, F, true> : k_assign_mfma<T, F, false>;
         if (!launch(2, assign_kernel, dim3(grid2), dim3(wpb2 * 64), 0, e, dstride, yoff, (const int32_t *)list,
-                    (const int32_t *)sc.counts, nslices, slice_px, npix, fa.tau4096 * 0x1p-7, h->tb,
+                    (const int32_t *)sc.counts, nslices, slice_px, npix, tau32, h->tb,
                     (const unsigned long long *)hcur, sc.hlast, Bw, Bh, cut, h->cap, cents, num, labels, score,
-                    (int32_t)(h->search_mode == 1)))
+                    force_exact))
             return CPE_ERR_HIP;
     } else {
         // launch 2 (larger grids): the stand-alone peak kernel, then the
-        // generic assignment; the stage events bracket both (start of the
+        // assignment on its plan; the stage events bracket both (start of the
         // first, end of the second)
         if (fail_at == 2) return CPE_ERR_HIP;
-        const PeakOut po{cents, num, sc.peaks, sc.kinfo};
-        const size_t plds = (size_t)nb * 8 + (size_t)max_peaks(Bw, Bh) * 4;
+        const size_t plds = (size_t)(Bw + 2) * (Bh + 2) * 8;
+        const int max_bat = max_batches(Bw, Bh);
         if (h->stage_on)
             hipExtLaunchKernelGGL(k_peaks, dim3(1), dim3(1024), (uint32_t)plds, stream, h->stage_ev[4], nullptr, 0u,
                                   (const unsigned long long *)hcur, sc.hlast, Bw, Bh, cut, h->cap, h->tb.cx,
-                                  h->tb.cy, po);
+                                  h->tb.cy, cents, num, sc.plan, max_bat);
         else
             hipLaunchKernelGGL(k_peaks, dim3(1), dim3(1024), plds, stream, (const unsigned long long *)hcur,
-                               sc.hlast, Bw, Bh, cut, h->cap, h->tb.cx, h->tb.cy, po);
+                               sc.hlast, Bw, Bh, cut, h->cap, h->tb.cx, h->tb.cy, cents, num, sc.plan, max_bat);
         if (hipGetLastError() != hipSuccess) return CPE_ERR_HIP;
-        const size_t fixed2 = generic_assign_fixed(Bw, Bh, F, max_peaks(Bw, Bh));
-        const int tp2 = pick_tile(fixed2, (size_t)Bw * 4, 120 * 1024);     // per pixel: its column distances
-        const size_t lds2 = fixed2 + (size_t)Bw * tp2 * 4;
-        const int64_t tiles2 = ((int64_t)npix + tp2 - 1) / tp2;
-        const int grid2 = (int)(tiles2 < 2048 ? tiles2 : 2048);
-        auto assign_kernel = k_assign_generic<T, F>;
+        const int64_t wgs2 = (tiles + kBigWpb - 1) / kBigWpb;
+        const int grid2 = (int)(wgs2 < kAssignGrid ? wgs2 : kAssignGrid);
+        const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels<T, F>);
+        auto assign_kernel = fast ? k_assign_big<T, F, true> : k_assign_big<T, F, false>;
         if (h->stage_on)
-            hipExtLaunchKernelGGL(assign_kernel, dim3(grid2), dim3(tp2), (uint32_t)lds2, stream, nullptr,
+            hipExtLaunchKernelGGL(assign_kernel, dim3(grid2), dim3(kBigWpb * 64), 0u, stream, nullptr,
                                   h->stage_ev[5], 0u, e, dstride, yoff, (const int32_t *)list,
-                                  (const int32_t *)sc.counts, nslices, slice_px, npix, fa.tau4096, h->tb, Bw, Bh,
-                                  (const int32_t *)sc.peaks, (const int32_t *)sc.kinfo, cents, labels, score);
+                                  (const int32_t *)sc.counts, nslices, slice_px, npix, tau32, h->tb,
+                                  (const BigPlan *)sc.plan, max_bat, cents, labels, score, force_exact);
         else
-            hipLaunchKernelGGL(assign_kernel, dim3(grid2), dim3(tp2), lds2, stream, e, dstride, yoff,
-                               (const int32_t *)list, (const int32_t *)sc.counts, nslices, slice_px, npix,
-                               fa.tau4096, h->tb, Bw, Bh, (const int32_t *)sc.peaks, (const int32_t *)sc.kinfo, cents,
-                               labels, score);
+            hipLaunchKernelGGL(assign_kernel, dim3(grid2), dim3(kBigWpb * 64), 0, stream, e, dstride, yoff,
+                               (const int32_t *)list, (const int32_t *)sc.counts, nslices, slice_px, npix, tau32,
+                               h->tb, (const BigPlan *)sc.plan, max_bat, cents, labels, score, force_exact);
         if (hipGetLastError() != hipSuccess) return CPE_ERR_HIP;
     }
     return CPE_OK;
