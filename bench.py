@@ -378,7 +378,7 @@ def sweep(steps, warmup):
         s, fr, ms, st, by, ws = bench_config(5, steps, warmup, bins=b, th=th, loaded=loaded, min_warm_ms=150.0)
         out["bins_sweep"].append({"workload": s.name, "bins": b, "ms_per_frame": round(ms, 5),
                                   "frames_per_s": round(1000.0 / ms, 1), "workspace_bytes": ws,
-                                  "path": "matrix-core" if b <= 32 else "matrix-core vote, generic assignment",
+                                  "path": "matrix-core" if b <= 32 else "matrix-core, passes over 32 x 32 blocks",
                                   "stages_ms": {k: round(v, 5) for k, v in st.items()},
                                   "paper_ms_orin_nano_fp32": PAPER_TABLE1_MS[b]})
     del loaded

@@ -323,16 +323,17 @@ __device__ __forceinline__ f16x8 palette_operand(const uint32_t *__restrict__ po
     return *reinterpret_cast<const f16x8 *>(pop + (((ax * kAxisKinds<F> + k) * 64 + lane) * 4));
 }
 
-// Word group i (16 bytes) of the LDS palette operands [axis][kAxisKinds][64]
-// [16] for the x bins of block bx and the y bins of block by, from the table
-// [axis][kMaxBinBlocks][kPopKinds][64][16]; PLUS1: with the constants of S +
-// 1 instead of S.
-template <int F, bool PLUS1>
+// Word group i (16 bytes) of the LDS palette operands [NX + 1][kAxisKinds]
+// [64][16] for the x bins of the NX blocks from bx on (the last one again past
+// the table) and the y bins of block by, from the table [axis]
+// [kMaxBinBlocks][kPopKinds][64][16]; PLUS1: with the constants of S + 1
+// instead of S.
+template <int F, int NX, bool PLUS1>
 __device__ __forceinline__ u32x4 pop_block(const uint32_t *__restrict__ pop, int i, int bx, int by)
 {
-    constexpr int kAxis = kAxisKinds<F> * 64;             // 16-byte groups per axis
-    const int ax = i / kAxis, r = i % kAxis, k = r >> 6;
-    const int blk = ax ? by : bx;
+    constexpr int kAxis = kAxisKinds<F> * 64;             // 16-byte groups per block
+    const int part = i / kAxis, r = i % kAxis, k = r >> 6, ax = part == NX ? 1 : 0;
+    const int blk = ax ? by : min(bx + part, kMaxBinBlocks - 1);
     const int kind = k == 0 ? 0 : k == 1 ? (PLUS1 ? 2 : 1) : k + 1;
     return reinterpret_cast<const u32x4 *>(pop)[((ax * kMaxBinBlocks + blk) * kPopKinds + kind) * 64 + (r & 63)];
 }
@@ -390,13 +391,13 @@ constexpr int kHStride = kMfmaBins + 1;
 // middle accumulator grows by at most 2^15 per pixel, 2^20 per tile.
 constexpr int kFoldTiles = 2047;
 
-// LDS bytes of k_vote_mfma: the weight table, the 64-bit histogram,
+// LDS bytes of k_vote_mfma (nx x blocks per pass): the weight table, the 64-bit histograms,
 // the palette operands, the slice prefix sums and counters; with the
 // compaction folded in (FUSED), the workgroup's own participating pixels.
 template <int F>
-constexpr size_t kVoteLds(bool fused)
+constexpr size_t kVoteLds(int nx, bool fused)
 {
-    return (size_t)kWKeys * 2 + kMfmaBins * kHStride * 8 + kPopBytes<F> + (kMaxSlices + 1) * 4 + 16 + (fused ? (size_t)kFusedMaxSeg * 4 : 0);
+    return (size_t)kWKeys * 2 + nx * kMfmaBins * kHStride * 8 + (nx + 1) * (kPopBytes<F> / 2) + (kMaxSlices + 1) * 4 + 16 + (fused ? (size_t)kFusedMaxSeg * 4 : 0);
 }
 
 // Eight foreground values from pixel p0 on (p0 a multiple of 8), in two
@@ -475,38 +476,50 @@ struct FusedArgs {
 // where three would spill.  Without a bound the compiler keeps the
 // accumulators in a separate AGPR allocation and the kernel drops to one wave
 // per SIMD.
+// Two blocks' accumulators (multi) leave two waves.
 template <typename T, int F>
-constexpr int kVoteWaves = (sizeof(T) == 2 && (F <= 8 || F == 16)) ? 3 : 2;
+constexpr int vote_waves(bool multi)
+{
+    return !multi && sizeof(T) == 2 && (F <= 8 || F == 16) ? 3 : 2;
+}
 // Waves per workgroup of the vote kernel: one workgroup per compute unit.
 template <typename T, int F>
-constexpr int kVoteWpb = 4 * kVoteWaves<T, F>;
+constexpr int vote_wpb(bool multi)
+{
+    return 4 * vote_waves<T, F>(multi);
+}
 //
 // Every workgroup adds its histogram into one of the kReplicas vote
 // histograms `hrep` (clear when the frame starts: an earlier launch cleared
 // them); the assignment launch that follows sums them and extracts the
 // peaks.  Workgroup 0 also resets the pixel counts of the centroid records,
 // which the assignment launch accumulates.
-// MULTI: grids above 32 x 32 bins (one pass per block of 32 x 32 bins);
-// otherwise the single block is compiled without the pass loop, whose
-// registers would otherwise spill.  FUSED: the launch lists the
-// participating pixels itself (FusedArgs); list and counts are then unused.
+// MULTI: grids above 32 x 32 bins, in passes over the workgroup's tiles of
+// two x blocks and one y block each (a single block is compiled without the
+// pass loop).  Each pass converts the input and weighs the y block anew, so
+// two x blocks per pass take 3 weight sets and one conversion where single
+// blocks take 4 and 2 (704 x 704 fp32 with 4 harmonics, 64 x 64 bins: 31.3
+// against 40.3 us).
+// FUSED: the launch lists the participating pixels itself (FusedArgs); list
+// and counts are then unused.
 template <typename T, int F, bool MULTI, bool FUSED>
-__global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_per_eu(kVoteWaves<T, F>))) void k_vote_mfma(
+__global__ __launch_bounds__((vote_wpb<T, F>(MULTI) * 64)) __attribute__((amdgpu_waves_per_eu(vote_waves<T, F>(MULTI)))) void k_vote_mfma(
     const T *__restrict__ emb, int32_t dstride, int32_t yoff, const int32_t *__restrict__ list,
     const int32_t *__restrict__ counts, int32_t nslices, int32_t slice_px, int32_t npix, Tables tb, int32_t Bw,
     int32_t Bh, unsigned long long *__restrict__ hrep,
     cpe_centroid *__restrict__ cents, int32_t cap, FusedArgs fz)
 {
-    static_assert(!(MULTI && FUSED), "the folded compaction serves single-block grids");
-    constexpr int kWpb = kVoteWpb<T, F>;
-    // blocks of 32 x 32 bins: one pass over the workgroup's tiles per block
+    constexpr int kWpb = vote_wpb<T, F>(MULTI), NX = MULTI ? 2 : 1;
+    constexpr int kBlockH = kMfmaBins * kHStride, kPopWords = (NX + 1) * (kPopBytes<F> / 2) / 4;
+    // passes over the workgroup's tiles: NX x blocks and one y block each
     const int nbx = MULTI ? (Bw + kMfmaBins - 1) / kMfmaBins : 1, nby = MULTI ? (Bh + kMfmaBins - 1) / kMfmaBins : 1;
+    const int npx = MULTI ? (nbx + NX - 1) / NX : 1;
     // All LDS is static, so that table addresses are compile-time constants.
-    __shared__ __align__(16) unsigned char smem[kVoteLds<F>(FUSED)];
+    __shared__ __align__(16) unsigned char smem[kVoteLds<F>(NX, FUSED)];
     uint16_t *s_wt = reinterpret_cast<uint16_t *>(smem);                              // [kWKeys] int8 limb pairs
-    unsigned long long *s_h = reinterpret_cast<unsigned long long *>(s_wt + kWKeys);  // [32][kHStride], b * kHStride + a
-    uint32_t *s_pop = reinterpret_cast<uint32_t *>(s_h + kMfmaBins * kHStride);      // palette operands
-    int *s_pref = reinterpret_cast<int *>(s_pop + kPopBytes<F> / 4);                  // [kMaxSlices + 1]
+    unsigned long long *s_h = reinterpret_cast<unsigned long long *>(s_wt + kWKeys);  // [NX][32][kHStride], b * kHStride + a
+    uint32_t *s_pop = reinterpret_cast<uint32_t *>(s_h + NX * kBlockH);              // palette operands: x blocks, y
+    int *s_pref = reinterpret_cast<int *>(s_pop + kPopWords);                         // [kMaxSlices + 1]
     int *s_next = s_pref + kMaxSlices + 1;                                            // next tile of the run
     int *s_cnt = s_next + 1;                                                          // FUSED: [2] pixels listed (LDS, global)
     int *s_list = s_pref + kMaxSlices + 5;                                            // FUSED: [kFusedMaxSeg]
@@ -621,9 +634,9 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
             const int i = k * kThreads + tid;
             if (i < kN) reinterpret_cast<u32x4 *>(s_wt)[i] = w[k];
         }
-        for (int i = tid; i < kMfmaBins * kHStride; i += kThreads) s_h[i] = 0ull;
-        for (int i = tid; i < kPopBytes<F> / 16; i += kThreads)
-            reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, true>(tb.pop, i, 0, 0);
+        for (int i = tid; i < NX * kBlockH; i += kThreads) s_h[i] = 0ull;
+        for (int i = tid; i < kPopWords / 4; i += kThreads)
+            reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, NX, true>(tb.pop, i, 0, 0);
         if (tid == 0) *s_next = 0;
         if (!FUSED && list) nlist = slice_scan(sl, nslices, s_pref);
     }
@@ -639,78 +652,92 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
         block_run(ntiles, blockIdx.x, gridDim.x, t0, tend);
     }
 
-    i32x16 acc2 = {}, acc1 = {}, acc0 = {};       // sums of nh nh, nh lo + lo nh, lo lo
+    i32x16 acc2[NX] = {}, acc1[NX] = {}, acc0[NX] = {};       // sums of nh nh, nh lo + lo nh, lo lo
     int ntile = 0;
 
-    // Add the limb sums into the workgroup's histogram (this wave owns every
+    // Add the limb sums into the workgroup's histograms (this wave owns every
     // (a, b) exactly once, so its own atomics never collide).
     auto fold = [&]() {
 #pragma unroll
-        for (int r = 0; r < 16; r++) {
-            const long long v = (long long)acc2[r] * 65536 - (long long)acc1[r] * 256 + acc0[r];
-            atomicAdd(&s_h[ln * kHStride + acc_row(r, g)], (unsigned long long)v);
-            acc2[r] = acc1[r] = acc0[r] = 0;
-        }
+        for (int x = 0; x < NX; x++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const long long v = (long long)acc2[x][r] * 65536 - (long long)acc1[x][r] * 256 + acc0[x][r];
+                atomicAdd(&s_h[x * kBlockH + ln * kHStride + acc_row(r, g)], (unsigned long long)v);
+                acc2[x][r] = acc1[x][r] = acc0[x][r] = 0;
+            }
     };
 
-    // Weight limbs (lo | nh << 8) of the 16 (pixel, bin) results of one axis:
-    // the binary32 bits of kScale (S + 1) give the bucket.
-    auto weights = [&](const f32x16 &A, const f32x16 &R, uint32_t (&e)[16]) {
+    // Weight limbs (lo | nh << 8) of the 16 (pixel, bin) results of one block
+    // (palette operands `part`): the binary32 bits of kScale (S + 1) give the
+    // bucket.
+    auto weights = [&](const AxisOp<T, F> &X, f16x8 e8, int part, uint32_t (&e)[16]) {
+        f16x8 P[kAxisKinds<F>];
+#pragma unroll
+        for (int k = 0; k < kAxisKinds<F>; k++) P[k] = palette_operand<F>(s_pop, part, k, lane);
+        f32x16 A, R;
+        axis_products<T, F, true>(X, e8, P, A, R);
 #pragma unroll
         for (int r = 0; r < 16; r++) e[r] = s_wt[(__float_as_uint(assemble(A[r], R[r])) >> 15) & (kWKeys - 1)];
     };
+    // The 16 pixels of this lane as the bytes of two operands.
+    struct Limbs {
+        i32x4 lo, nh;
+    };
+    auto limbs = [](const uint32_t (&e)[16]) {
+        u32x4 l, h;
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            const uint32_t w01 = e[4 * s] | e[4 * s + 1] << 16, w23 = e[4 * s + 2] | e[4 * s + 3] << 16;
+            l[s] = __builtin_amdgcn_perm(w23, w01, 0x06040200u);
+            h[s] = __builtin_amdgcn_perm(w23, w01, 0x07050301u);
+        }
+        return Limbs{__builtin_bit_cast(i32x4, l), __builtin_bit_cast(i32x4, h)};
+    };
 
     // One tile of up to 32 pixels (queue slot m = lane & 31) from prefetched
-    // input; `next` reuses the input registers once they are converted.
-    auto tile = [&](RawSlices<T, F> &raw, int nvalid, auto next) {
+    // input; `next` reuses the input registers once they are converted; nx: x
+    // blocks of this pass.
+    auto tile = [&](RawSlices<T, F> &raw, int nvalid, int nx, auto next) {
         PixOps<T, F> X;
         X.from(raw);
         next();
-        uint32_t ex[16], ey[16];
+        uint32_t e[16];
+        Limbs x[NX];
 #pragma unroll
-        for (int ax = 0; ax < 2; ax++) {
-            f16x8 P[kAxisKinds<F>];
-#pragma unroll
-            for (int k = 0; k < kAxisKinds<F>; k++) P[k] = palette_operand<F>(s_pop, ax, k, lane);
-            f32x16 A, R;
-            axis_products<T, F, true>(X.ax[ax], X.e, P, A, R);
-            weights(A, R, ax ? ey : ex);
+        for (int i = 0; i < NX; i++) {
+            if (i > 0 && i >= nx) break;
+            weights(X.ax[0], X.e, i, e);
+            x[i] = limbs(e);
         }
+        weights(X.ax[1], X.e, NX, e);
         if (nvalid < 32) {        // pixels past the end of the list vote nothing
             // (kept a real branch: only the last tile of a round is partial)
             __asm__ volatile("" ::: "memory");
 #pragma unroll
             for (int r = 0; r < 16; r++)
-                if (acc_row(r, g) >= nvalid) ex[r] = 0u;
+                if (acc_row(r, g) >= nvalid) e[r] = 0u;
         }
+        const Limbs y = limbs(e);
         // vote: K = the 16 pixels of this lane, one byte each
-        u32x4 xl, xh, yl, yh;
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const int r = 4 * s;
-            const uint32_t x01 = ex[r] | ex[r + 1] << 16, x23 = ex[r + 2] | ex[r + 3] << 16;
-            const uint32_t y01 = ey[r] | ey[r + 1] << 16, y23 = ey[r + 2] | ey[r + 3] << 16;
-            xl[s] = __builtin_amdgcn_perm(x23, x01, 0x06040200u);
-            xh[s] = __builtin_amdgcn_perm(x23, x01, 0x07050301u);
-            yl[s] = __builtin_amdgcn_perm(y23, y01, 0x06040200u);
-            yh[s] = __builtin_amdgcn_perm(y23, y01, 0x07050301u);
+        for (int i = 0; i < NX; i++) {
+            if (i > 0 && i >= nx) break;
+            acc2[i] = mfma8(x[i].nh, y.nh, acc2[i]);
+            acc1[i] = mfma8(x[i].nh, y.lo, acc1[i]);
+            acc0[i] = mfma8(x[i].lo, y.lo, acc0[i]);
+            acc1[i] = mfma8(x[i].lo, y.nh, acc1[i]);
         }
-        const i32x4 XL = __builtin_bit_cast(i32x4, xl), XH = __builtin_bit_cast(i32x4, xh);
-        const i32x4 YL = __builtin_bit_cast(i32x4, yl), YH = __builtin_bit_cast(i32x4, yh);
-        acc2 = mfma8(XH, YH, acc2);
-        acc1 = mfma8(XH, YL, acc1);
-        acc0 = mfma8(XL, YL, acc0);
-        acc1 = mfma8(XL, YH, acc1);
     };
 
-    for (int blk = 0; blk < nbx * nby; blk++) {
-        const int bx = blk % nbx, by = blk / nbx;
+    for (int blk = 0; blk < npx * nby; blk++) {
+        const int bx = NX * (blk % npx), by = blk / npx, nx = min(NX, nbx - bx);
         if (MULTI && blk > 0) {
             // the next block: its palette operands, a clear histogram and tile
             // counter (the previous pass has flushed)
-            for (int i = tid; i < kMfmaBins * kHStride; i += blockDim.x) s_h[i] = 0ull;
-            for (int i = tid; i < kPopBytes<F> / 16; i += blockDim.x)
-                reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, true>(tb.pop, i, bx, by);
+            for (int i = tid; i < NX * kBlockH; i += blockDim.x) s_h[i] = 0ull;
+            for (int i = tid; i < kPopWords / 4; i += blockDim.x)
+                reinterpret_cast<u32x4 *>(s_pop)[i] = pop_block<F, NX, true>(tb.pop, i, bx, by);
             if (tid == 0) *s_next = 0;
             __syncthreads();
         }
@@ -735,7 +762,7 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
         }
         while (t < tend) {
             int tnn = tend;
-            tile(raw, min(32, n - 32 * t), [&]() {
+            tile(raw, min(32, n - 32 * t), nx, [&]() {
                 if (tn < tend) {
                     raw.load(emb + (size_t)idx * dstride, yoff, g);
                     tnn = take_tile(s_next, lane, t0, kWpb);
@@ -754,9 +781,10 @@ __global__ __launch_bounds__((kVoteWpb<T, F> * 64)) __attribute__((amdgpu_waves_
         __syncthreads();
         const int nb = Bw * Bh;
         unsigned long long *dst = hrep + (size_t)(blockIdx.x % kReplicas) * nb;
-        for (int i = tid; i < kMfmaBins * kMfmaBins; i += blockDim.x) {
-            const int b = kMfmaBins * by + i / kMfmaBins, a = kMfmaBins * bx + i % kMfmaBins;
-            const unsigned long long v = s_h[(i / kMfmaBins) * kHStride + i % kMfmaBins];
+        for (int i = tid; i < nx * kMfmaBins * kMfmaBins; i += blockDim.x) {
+            const int x = i / (kMfmaBins * kMfmaBins), c = i % kMfmaBins, r = i / kMfmaBins % kMfmaBins;
+            const int b = kMfmaBins * by + r, a = kMfmaBins * (bx + x) + c;
+            const unsigned long long v = s_h[x * kBlockH + r * kHStride + c];
             if (a < Bw && b < Bh && v) atomicAdd(dst + b * Bw + a, v);
         }
         __syncthreads();
@@ -1092,7 +1120,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
 #pragma unroll
     for (int k = 0; k < kPopPer; k++) {
         const int i = k * kThreads + tid;
-        pop[k] = pop_block<F, false>(tb.pop, i < kPopBytes<F> / 16 ? i : 0, 0, 0);
+        pop[k] = pop_block<F, 1, false>(tb.pop, i < kPopBytes<F> / 16 ? i : 0, 0, 0);
     }
     // This wave's search arrays, [slot][kKeyStride] per axis: x key of column
     // slot j, pixel m at kx[j * kKeyStride + m], y distance of row slot j at

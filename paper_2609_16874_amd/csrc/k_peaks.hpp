@@ -254,7 +254,7 @@ namespace {   // one private copy per translation unit that launches it
 // centroid records, K and the summed histogram.  The launch is a chain of
 // latencies: its loads are issued kUnroll bins at a time, and everything after
 // the masks is local to a lane's rows.
-__global__ __launch_bounds__(1024) void k_peaks(const unsigned long long *__restrict__ hrep,
+__global__ __launch_bounds__(1024) __attribute__((unused)) void k_peaks(const unsigned long long *__restrict__ hrep,
                                                 unsigned long long *__restrict__ hlast, int32_t Bw, int32_t Bh,
                                                 long long cut, int32_t cap, const float *__restrict__ cx,
                                                 const float *__restrict__ cy, cpe_centroid *__restrict__ cents,

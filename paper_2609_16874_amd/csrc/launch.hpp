@@ -75,14 +75,14 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         sc.dirty[1 - par] = 0;
         *sc.parity = 1 - par;
     };
-    constexpr int wpb = kVoteWpb<T, F>;
+    const int wpb = vote_wpb<T, F>(!mfma);
     const int64_t tiles = ((int64_t)npix + 31) / 32;
     int32_t *list = sc.list;
     int nslices, slice_px;
     const FusedPlan fp = fused_plan(npix);
-    if (mfma && fp.ok) {
-        // Two launches.  Launch 0 would be the compaction, which the vote
-        // launch does itself here: its events record back to back.
+    if (fp.ok) {
+        // Launch 0 would be the compaction, which the vote launch does itself
+        // here: its events record back to back.
         if (fail_at == 0) return CPE_ERR_HIP;
         if (h->stage_on) {
             if (hipEventRecord(h->stage_ev[0], stream) != hipSuccess ||
@@ -94,7 +94,8 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         const FusedArgs fz{fg, fg_thr, fp.slice, fp.seg_cap, fp.rot, list, sc.counts, labels, score,
                            hnext, (int32_t)nclear};
         if (sc.dirty[par] < nused) sc.dirty[par] = nused;
-        if (!launch(1, k_vote_mfma<T, F, false, true>, dim3(fp.grid), dim3(wpb * 64), 0, e, dstride, yoff,
+        auto vote_kernel = mfma ? k_vote_mfma<T, F, false, true> : k_vote_mfma<T, F, true, true>;
+        if (!launch(1, vote_kernel, dim3(fp.grid), dim3(wpb * 64), 0, e, dstride, yoff,
                     (const int32_t *)nullptr, (const int32_t *)nullptr, 0, 0, npix, h->tb, Bw, Bh, hcur, cents,
                     h->cap, fz))
             return CPE_ERR_HIP;
@@ -121,7 +122,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
                         sc.counts, labels, score, hnext, (int32_t)nclear);
         if (!ok) return CPE_ERR_HIP;
         flip();
-        // launch 1: recovery + voting, one pass per block of 32 x 32 bins;
+        // launch 1: recovery + voting, in passes over blocks of 32 x 32 bins;
         // grid: at most one workgroup per compute unit, no more waves than tiles
         const int64_t wgs = (tiles + wpb - 1) / wpb;
         const int grid = (int)(wgs < kVoteGrid ? wgs : kVoteGrid);
