@@ -470,17 +470,17 @@ struct FusedArgs {
     int32_t nnext;
 };
 
-// Waves per SIMD the register allocation must allow: three for fp16 inputs
-// with up to 8 or exactly 16 harmonics (one workgroup of 12 waves per compute
-// unit), two otherwise (fp32 residual operands, scalar channel loads),
-// where three would spill.  Without a bound the compiler keeps the
-// accumulators in a separate AGPR allocation and the kernel drops to one wave
-// per SIMD.
-// Two blocks' accumulators (multi) leave two waves.
+// Waves per SIMD the register allocation must allow: three (one workgroup of
+// 12 waves per compute unit) for fp16 inputs and fp32 ones with up to 8
+// harmonics (1500 x 1500 fp32 with 8: 77.3 against 79.1 us per frame with two;
+// 900 x 900 fp16 with 10: 38.7 against 40.0), two otherwise and for two
+// blocks' accumulators (multi), which would spill.  Without a bound the
+// compiler keeps the accumulators in a separate AGPR allocation and the
+// kernel drops to one wave per SIMD.
 template <typename T, int F>
 constexpr int vote_waves(bool multi)
 {
-    return !multi && sizeof(T) == 2 && (F <= 8 || F == 16) ? 3 : 2;
+    return !multi && (F <= 8 || sizeof(T) == 2) ? 3 : 2;
 }
 // Waves per workgroup of the vote kernel: one workgroup per compute unit.
 template <typename T, int F>
@@ -1115,6 +1115,15 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
     if (list) slice_load(counts, nslices, sl);
     PeakBins<kWpb2> pb;
     pb.load(hcur, Bw, Bh);
+    // workgroup 0 writes the records: the bin centres it needs, loaded now
+    float cx[PeakBins<kWpb2>::N], cy[PeakBins<kWpb2>::N];
+#pragma unroll
+    for (int u = 0; u < PeakBins<kWpb2>::N; u++) {
+        int a, b;
+        const bool in = PeakBins<kWpb2>::pair(u, a, b) && blockIdx.x == 0 && a < Bw && b < Bh;
+        cx[u] = in ? tb.cx[a] : 0.0f;
+        cy[u] = in ? tb.cy[b] : 0.0f;
+    }
     constexpr int kPopPer = (kPopBytes<F> / 16 + kThreads - 1) / kThreads;
     u32x4 pop[kPopPer];
 #pragma unroll
@@ -1167,8 +1176,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
                 cpe_centroid *c = cents + pl.rowfirst[b] + __popc(m & ((1u << a) - 1u));
                 c->bin_x = a;
                 c->bin_y = b;
-                c->x = tb.cx[a];
-                c->y = tb.cy[b];
+                c->x = cx[u];
+                c->y = cy[u];
                 c->score = (double)pb.sum[u] * 0x1p-30;
                 c->reserved = 0;
             }
