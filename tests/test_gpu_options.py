@@ -206,6 +206,23 @@ def test_masks_ragged_sizes(H, W):
     dec.close()
 
 
+@pytest.mark.parametrize("H,W", [(1, 15), (1, 17), (19, 53), (9, 112), (1, 1009), (6, 169), (37, 109), (12, 341)])
+def test_masks_piece_edges(H, W):
+    """One pixel less and more than a 16-byte piece and than a wave's 63
+    pieces, several workgroups; 18 masks start at every offset from a 16-byte
+    boundary that H W allows and end inside a group of eight."""
+    rng = np.random.default_rng(H * W)
+    cap = 20
+    dec = native().Decoder(H, W, 1, "f32", np.array([2 * math.pi / W]), np.array([2 * math.pi / H]), 8, 5, cap)
+    lab = rng.integers(-2, cap + 3, size=(H, W)).astype(np.int32)
+    lab.reshape(-1)[::7] = np.array([2**31 - 1, -(2**31)] * (H * W), dtype=np.int32)[: len(lab.reshape(-1)[::7])]
+    ld = torch.from_numpy(lab).cuda()
+    for first, count in ((1, 18), (0, 9)):
+        m = _masks(dec, ld, first, count, H, W)
+        assert np.array_equal(m, (lab[None] == (first + 1 + np.arange(count))[:, None, None]).astype(np.uint8))
+    dec.close()
+
+
 def test_option_and_mask_argument_errors():
     nat = native()
     spec = synth.CONFIGS[0]
