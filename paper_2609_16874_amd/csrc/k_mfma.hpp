@@ -870,8 +870,7 @@ struct Labeller {
 //
 // Let every x and y be within one binary32 step (at most 2^-23 of the
 // value) of the correctly rounded root: the hardware's root is
-// (cpe_check_sqrt verifies sqrt_cr, which only tries it and its two
-// neighbours, on every input).  Then x + y lies within relative 2^-23 of
+// (cpe_check_sqrt tries every input).  Then x + y lies within relative 2^-23 of
 // the exact sum, and s within g = 3 2^-24 + 2^-47 of the batch's true
 // minimum D.  If every other batch's s exceeds the winner's s_w by
 // kFastGap steps (each more than 2^-24 s_w), so by more than 2g / (1 - g)
