@@ -265,9 +265,10 @@ cpe_status cpe_decode_test_fail_launch(cpe_decoder *h, int32_t launch);
 
 /*
  * Testing: the assignment search of later label-only decodes on this handle
- * (no score map, tau = +inf, grids up to 32 x 32 bins).  mode 0 (default):
- * the fast search (hardware square roots, near ties recomputed exactly) on
- * frames of at least 2^20 pixels, the exact search on smaller ones; 1: the
+ * (no score map, tau = +inf).  mode 0 (default): the fast search (hardware
+ * square roots, near ties recomputed exactly) on frames of at least 2^18
+ * pixels with up to 8 harmonics and of 2^19 for binary16 inputs with more, the
+ * exact search otherwise; 1: the
  * fast-search kernel at any size with every tile treated as a near tie,
  * i.e. recomputed with correctly rounded distances and the exact search;
  * 2: the fast search at any size.  The labels are the same in every mode.
@@ -279,10 +280,10 @@ cpe_status cpe_decode_test_search_mode(cpe_decoder *h, int32_t mode);
 size_t cpe_decode_workspace_bytes(const cpe_decoder *h);
 
 /*
- * Kernels each frame of this handle launches: 2 when the vote launch also
- * lists the participating pixels (frames of up to 2^21 pixels on grids up to
- * 32 x 32 bins), else 3 (numbered as for cpe_decode_set_stage_events); 0 for
- * NULL.
+ * Launches of each frame of this handle: 2 for frames of up to 2^21 pixels
+ * (whose vote launch also lists the participating pixels) on grids up to 32 x
+ * 32 bins, else 3 (numbered as for cpe_decode_set_stage_events, whose launch
+ * 2 is two kernels above 32 x 32 bins); 0 for NULL.
  */
 int32_t cpe_decode_launch_count(const cpe_decoder *h);
 
@@ -296,9 +297,8 @@ int32_t cpe_decode_launch_count(const cpe_decoder *h);
  * foreground channel), 1 = recovery + voting, 2 = peak extraction +
  * assignment (one kernel for grids up to 32 x 32 bins; above, events 4 and 5
  * bracket the peak kernel and the assignment kernel that follows it).
- * Frames of up to 2^21 pixels on grids up to 32 x 32 bins take two
- * launches: kernel 1 also compacts and clears, and events 0 and 1 are
- * recorded back to back, with no kernel between them.  `n_events` must be
+ * On frames of up to 2^21 pixels kernel 1 also compacts and clears, and
+ * events 0 and 1 are recorded back to back, with no kernel between them.  `n_events` must be
  * CPE_STAGE_EVENTS;
  * the caller owns the events and must keep them alive while set.  NULL
  * switches the recording off.

@@ -1,8 +1,7 @@
 // k_compact.hpp -- the participating set S of Eq6 as a compact pixel list.
 //
-// One launch before the vote in frames of three launches (frames above
-// kFusedMaxPixels pixels, grids above 32 x 32 bins; the vote launch lists
-// the pixels itself otherwise).  Workgroup s of the grid owns the
+// One launch before the vote in frames above kFusedMaxPixels pixels (the
+// vote launch lists the pixels of smaller ones itself).  Workgroup s of the grid owns the
 // pixel range [s R, (s + 1) R) (R a multiple of 8192) and writes the indices
 // of its participating pixels, in raster order, to its slice list[s R ..]
 // and their number to counts[s]; every lane tests 8 consecutive foreground

@@ -446,7 +446,7 @@ __device__ __forceinline__ void load8_values(const T *fg, int p0, int lim, bool 
 }
 
 // The compaction folded into the vote launch (frames of up to kFusedMaxPixels
-// pixels, grids up to 32 x 32).  Workgroup b lists the participating pixels
+// pixels).  Workgroup b lists the participating pixels
 // twice: those of its range b * seg_cap .. (b + 1) * seg_cap - 1 of the
 // frame (seg_cap a multiple of 8) into list[b * seg_cap ..], their number
 // into counts[b] -- the assignment launch reads these segments as its slices,

@@ -188,8 +188,8 @@ class Decoder:
         return library().cpe_decode_test_fail_launch(self._h, int(launch))
 
     def test_search_mode(self, mode: int) -> int:
-        """cpe_decode_test_search_mode: 0 default (fast search on frames of
-        2^20 pixels or more), 1 every tile recomputed exactly, 2 the fast
+        """cpe_decode_test_search_mode: 0 default (fast search on larger
+        frames), 1 every tile recomputed exactly, 2 the fast
         search at any size."""
         return library().cpe_decode_test_search_mode(self._h, int(mode))
 
