@@ -20,11 +20,12 @@ constexpr int64_t kAssignGrid = 256;
 // labels are requested: where a wave has more than one tile the shorter
 // instruction stream pays, below it a near tie's second pass costs more.
 // Measured (exact, fast search, us per frame): 8 harmonics or fewer, 256 x 256
-// fp32 18.8, 19.6; 512 x 512 fp32 24.0, 24.1; 479 x 641 fp16 32.1, 30.2; 704 x
-// 704 fp32 30.6, 28.9; above, 512 x 520 fp16 24.0, 24.2; 640 x 640 fp16 29.3,
-// 29.2; 900 x 900 fp16 41.1, 39.9.
+// fp32 18.5, 19.3; 512 x 512 fp32 25.8, 26.8; 479 x 641 fp16 23.1, 22.8; 704 x
+// 704 fp32 31.8, 31.0; 640 x 640 fp16 26.7, 25.7; above, 512 x 520 fp16 25.2,
+// 25.8; from 2^19 to 2^20 pixels the two are within 1.2 %, either way (900 x
+// 900 46.6, 47.1; 1024 x 1024 53.2, 53.3); 1024 x 2048 61.2, 60.3.
 // fp32 inputs with more than 8 harmonics spill registers in the fast kernel
-// (640 x 640: 36.4, 39.4) and keep the exact one.
+// (640 x 640: 38.9, 42.5) and keep the exact one.
 template <typename T, int F>
 constexpr int64_t kFastSearchPixels = F <= 8 ? 1LL << 18 : sizeof(T) == 2 ? 1LL << 19 : INT64_MAX;
 
