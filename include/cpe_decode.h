@@ -276,6 +276,15 @@ cpe_status cpe_decode_test_fail_launch(cpe_decoder *h, int32_t launch);
  */
 cpe_status cpe_decode_test_search_mode(cpe_decoder *h, int32_t mode);
 
+/*
+ * Testing: with on = 1, later decodes on this handle take the launches of
+ * frames above 2^21 pixels at any size: the participating pixels are listed
+ * by a launch of their own before the vote (without a foreground channel that
+ * launch only clears histograms, and there is no list).  0 (default): by
+ * size.  The outputs are the same.  CPE_ERR_INVALID_ARG for another value.
+ */
+cpe_status cpe_decode_test_separate_list(cpe_decoder *h, int32_t on);
+
 /* Bytes of device memory the handle holds (constants + scratch). */
 size_t cpe_decode_workspace_bytes(const cpe_decoder *h);
 

@@ -377,6 +377,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     h->sc.list = reinterpret_cast<int32_t *>(d + o_list);
     h->fail_at = -1;
     h->search_mode = 0;
+    h->separate_list = false;
     *out = h;
     return CPE_OK;
 }
@@ -466,13 +467,20 @@ cpe_status cpe_decode_test_search_mode(cpe_decoder *h, int32_t mode)
     return CPE_OK;
 }
 
+cpe_status cpe_decode_test_separate_list(cpe_decoder *h, int32_t on)
+{
+    if (!h || (on != 0 && on != 1)) return CPE_ERR_INVALID_ARG;
+    h->separate_list = on == 1;
+    return CPE_OK;
+}
+
 size_t cpe_decode_workspace_bytes(const cpe_decoder *h) { return h ? h->dev_bytes : 0; }
 
 int32_t cpe_decode_launch_count(const cpe_decoder *h)
 {
     if (!h) return 0;
     const bool mfma = h->bins_w <= kMfmaBins && h->bins_h <= kMfmaBins;
-    return mfma && fused_plan((int64_t)h->H * h->W).ok ? 2 : 3;
+    return mfma && frame_plan(h).ok ? 2 : 3;
 }
 
 cpe_status cpe_decode_set_stage_events(cpe_decoder *h, hipEvent_t *events, int32_t n_events)

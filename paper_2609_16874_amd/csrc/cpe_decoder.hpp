@@ -83,6 +83,7 @@ struct cpe_decoder {
     size_t dirty[2];                     // words of each set that may be nonzero (sc.dirty points here)
     int fail_at;                         // test hook: the next decode stops before this launch (-1: none)
     int search_mode;                     // test hook: 0 default, 1 every tile exact, 2 fast search at any size
+    bool separate_list;                  // test hook: the pixels are listed by a launch of their own at any size
     hipEvent_t stage_ev[CPE_STAGE_EVENTS];
     bool stage_on;
     // per-tuple ablation (cpe_decode_naive): real palettes gamma(bin centre)
@@ -93,6 +94,12 @@ struct cpe_decoder {
 };
 
 namespace cpe {
+
+// The plan of this handle's frames (ok = false: a launch of its own lists the pixels).
+inline FusedPlan frame_plan(const cpe_decoder *h)
+{
+    return h->separate_list ? FusedPlan{} : fused_plan((int64_t)h->H * h->W);
+}
 
 // Arguments of one frame's launch sequence.
 struct FrameArgs {

@@ -80,7 +80,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
     const int64_t tiles = ((int64_t)npix + 31) / 32;
     int32_t *list = sc.list;
     int nslices, slice_px;
-    const FusedPlan fp = fused_plan(npix);
+    const FusedPlan fp = frame_plan(h);
     if (fp.ok) {
         // Launch 0 would be the compaction, which the vote launch does itself
         // here: its events record back to back.

@@ -29,7 +29,7 @@ EXPORTS = ("cpe_decode_create", "cpe_decode", "cpe_decode_ex", "cpe_decode_masks
            "cpe_status_string", "cpe_decode_get_tables", "cpe_decode_get_histogram", "cpe_decode_workspace_bytes",
            "cpe_decode_set_stage_events", "cpe_decode_naive", "cpe_check_sqrt",
            "cpe_decode_test_fail_launch", "cpe_decode_noalloc", "cpe_decode_launch_count",
-           "cpe_decode_test_search_mode")
+           "cpe_decode_test_search_mode", "cpe_decode_test_separate_list")
 STAGE_EVENTS = 6
 MFMA_BINS = 32
 
@@ -96,6 +96,8 @@ def library():
         lib.cpe_decode_test_fail_launch.argtypes = [P, i32]
         lib.cpe_decode_test_search_mode.restype = i32
         lib.cpe_decode_test_search_mode.argtypes = [P, i32]
+        lib.cpe_decode_test_separate_list.restype = i32
+        lib.cpe_decode_test_separate_list.argtypes = [P, i32]
         lib.cpe_check_sqrt.restype = i32
         lib.cpe_check_sqrt.argtypes = [P, P]
         _lib = lib
@@ -192,6 +194,11 @@ class Decoder:
         frames), 1 every tile recomputed exactly, 2 the fast
         search at any size."""
         return library().cpe_decode_test_search_mode(self._h, int(mode))
+
+    def test_separate_list(self, on: bool) -> int:
+        """cpe_decode_test_separate_list: list the pixels in a launch of their
+        own, as above 2^21 pixels."""
+        return library().cpe_decode_test_separate_list(self._h, int(on))
 
     def histogram(self, out, stream=None) -> int:
         return library().cpe_decode_get_histogram(self._h, _stream_ptr(stream), _ptr(out))
