@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kBigWpb * 64) __attribute__((amdgpu_waves_per_eu(kB
 
     auto distances = [&](auto exact, auto next) {
         PixOps<T, F> X;
-        X.from(raw);
+        X.from(raw, g);
         next();
 #pragma unroll
         for (int ax = 0; ax < 2; ax++) {
