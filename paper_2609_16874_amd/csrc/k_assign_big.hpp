@@ -109,8 +109,7 @@ __global__ __launch_bounds__(kBigWpb * 64) __attribute__((amdgpu_waves_per_eu(kB
         }
         return;
     }
-    int bits = kStepBits;                       // of the step of a batch, 8 batches per step
-    while ((8 << bits) < nbat) bits++;
+    const int bits = step_bits(nbat);
     const Batches bt{s_bo, s_bh, s_bk, nbat, real};
     const Labeller<true> out{labels, score_map, tau32, s_cnt, cents};
 
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(kBigWpb * 64) __attribute__((amdgpu_waves_per_eu(kB
         const int nvalid = min(32, n - 32 * t);
         if constexpr (FAST) {
             distances(std::false_type{}, next);
-            if (!search_tile<false, 0>(bt, kx, ky, lane, ip, nvalid, bits, force_exact, out)) {
+            if (!search_tile<false>(bt, kx, ky, lane, ip, nvalid, bits, force_exact, out)) {
                 raw.load(emb + (size_t)ip * dstride, yoff, g);          // this tile's rows again
                 distances(std::true_type{}, []() {});
                 if (tn < tend) raw.load(emb + (size_t)ipn * dstride, yoff, g);   // the next tile's rows again
@@ -159,7 +158,7 @@ __global__ __launch_bounds__(kBigWpb * 64) __attribute__((amdgpu_waves_per_eu(kB
             }
         } else {
             distances(std::true_type{}, next);
-            if (!search_tile<true, 0>(bt, kx, ky, lane, ip, nvalid, bits, force_exact, out))
+            if (!search_tile<true>(bt, kx, ky, lane, ip, nvalid, bits, force_exact, out))
                 search_exact<4095>(bt, kx, ky, lane, ip, nvalid, out);
         }
         t = tn;

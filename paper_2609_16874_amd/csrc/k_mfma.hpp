@@ -67,6 +67,7 @@
 #include "cpe_common.hpp"
 #include "k_compact.hpp"
 #include "k_peaks.hpp"
+#include "search_keys.hpp"
 
 namespace cpe {
 
@@ -118,9 +119,10 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 // search needs the second smallest batch sum to exceed the smallest: at
 // least 7 by its error bound (see k_assign_mfma).
 constexpr int kFastGap = 8;
-// Low bits of the search's keys that hold the step of a lane's batch.
+// Low bits of the search's keys that hold the step of a lane's batch: as many
+// as the frame's batches need (step_bits), at most this for grids up to 32 x 32.
 constexpr int kStepBits = 4;
-static_assert(8 << kStepBits >= kMaxBatchLds, "eight batches per step");
+static_assert(step_bits(kMaxBatchLds) == kStepBits, "eight batches per step");
 
 // Exchanges between the lanes of a wave: the upper half (the odd rows of 16
 // lanes) of a and the lower half (the even rows) of b swap places, so that a
@@ -868,7 +870,7 @@ struct Labeller {
 // pixels, and the next batch's offsets are read ahead.  Per pixel it keeps
 // the smallest binary32 sum s = fl(min x + y) of a batch and the second
 // smallest, as keys: the bits of s (which order like the sums) with the
-// batch's step in the low `bits` (BITS where it is known: kStepBits).  The first batch only initialises.
+// batch's step in the low `bits`.  The first batch only initialises.
 // The eight lanes of a pixel quad then merge in registers (half and row
 // swaps that leave a lane two pixels, one, then a rotation within the row
 // of 16), which leaves pixel m = 4 q + 2 (l >> 5) + (l >> 4 & 1) in lane l
@@ -881,7 +883,10 @@ struct Labeller {
 // minimum D.  If every other batch's s exceeds the winner's s_w by
 // kFastGap steps (each more than 2^-24 s_w), so by more than 2g / (1 - g)
 // s_w, its D is strictly larger (a sum of 0 is exact: any other distance
-// sum is at least 2^-7).  The keys show a gap of s less the step bits.
+// sum is at least 2^-7).  The keys show a gap of s less the step bits, hence as
+// few of them as the frame's batches need (always 4: 0.30 % of the tiles of a
+// 640 x 640 fp16 frame with outliers were undecided, with its 3 0.18 %; 1024 x
+// 2048, 16 harmonics, 75.2 against 74.2 us).
 // (Merging through LDS, with the batch in a register of its own per pixel
 // and the binary64 sums in the exact kernel, took 43 VALU instructions per
 // step instead of 31 and two LDS round trips more: 1024 x 2048, 16
@@ -891,12 +896,12 @@ struct Labeller {
 // smallest is strictly farther.  So a decided pixel has the label of the
 // exact sums.  EXACT (correctly rounded roots): the first column at the
 // batch's smallest x is the nearest, and its D is exact.
-template <bool EXACT, int BITS, bool BIG>
+template <bool EXACT, bool BIG>
 __device__ __forceinline__ bool search_tile(const Batches &bt, const uint32_t *kx, const uint32_t *ky, int lane, int pix,
                                             int nvalid, int bits, int force_exact, const Labeller<BIG> &out)
 {
-    const int sh = BITS ? BITS : bits;
-    const uint32_t step_mask = (1u << sh) - 1u;
+    uint32_t sum_mask = ~0u << bits;
+    __asm__ volatile("" : "+v"(sum_mask));  // a vector register: an instruction reads one scalar, the step
     __builtin_amdgcn_wave_barrier();
     int lo = lane;
     __asm__ volatile("" : "+v"(lo));        // recomputed per tile, not held across the loop
@@ -908,7 +913,7 @@ __device__ __forceinline__ bool search_tile(const Batches &bt, const uint32_t *k
     uint32_t hb = bt.bh[j0];
     // the sums of the batch at o, hb; then the offsets of batch `next`
     // (past the list: bytes of the arrays behind it, never used)
-    auto sums = [&](int next, uint32_t (&sm)[4]) {
+    auto keys = [&](int it, int next, uint32_t (&key)[4]) {
         const u32x4 v0 = *reinterpret_cast<const u32x4 *>(kxq + o.x);
         const u32x4 v1 = *reinterpret_cast<const u32x4 *>(kxq + o.y);
         const u32x4 v2 = *reinterpret_cast<const u32x4 *>(kxq + o.z);
@@ -919,20 +924,20 @@ __device__ __forceinline__ bool search_tile(const Batches &bt, const uint32_t *k
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             const uint32_t m = min(min(v0[e], v1[e]), min(v2[e], v3[e]));
-            sm[e] = __float_as_uint(__uint_as_float(m) + __uint_as_float(yd[e])) & ~step_mask;
+            const uint32_t s = __float_as_uint(__uint_as_float(m) + __uint_as_float(yd[e]));
+            key[e] = (s & sum_mask) | (uint32_t)it;
         }
     };
-    sums(j0 + 8, b);
+    keys(0, j0 + 8, b);
 #pragma unroll
     for (int e = 0; e < 4; e++) s2[e] = 0x7f800000u;
     for (int it = 1; 8 * it < bt.n; it++) {
-        uint32_t sm[4];
-        sums(8 * it + 8 + j0, sm);
+        uint32_t key[4];
+        keys(it, 8 * it + 8 + j0, key);
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const uint32_t key = sm[e] | (uint32_t)it;
-            s2[e] = max(min(b[e], s2[e]), min(max(b[e], s2[e]), key));      // their median
-            b[e] = min(b[e], key);
+            s2[e] = max(min(b[e], s2[e]), min(max(b[e], s2[e]), key[e]));      // their median
+            b[e] = min(b[e], key[e]);
         }
     }
     // merge (b, s2, lane j) of two parts of one pixel's batches
@@ -959,7 +964,7 @@ __device__ __forceinline__ bool search_tile(const Batches &bt, const uint32_t *k
     p[0] = merge(p[0], {row_ror8(p[0].b), row_ror8(p[0].s2), row_ror8(p[0].j)});   // j bit 0
     const int m = 4 * q + 2 * (lo >> 5) + ((lo >> 4) & 1);
     const int pm = __shfl(pix, m);
-    const int bi = (int)(8u * (p[0].b & step_mask) + p[0].j);
+    const int bi = (int)(8u * (p[0].b & ~sum_mask) + p[0].j);
     const u32x4 ow = bt.bo[bi];
     const int k0 = (int)bt.bk[bi];
     const unsigned char *kxl = reinterpret_cast<const unsigned char *>(kx + m);
@@ -969,7 +974,7 @@ __device__ __forceinline__ bool search_tile(const Batches &bt, const uint32_t *k
     const uint32_t w3 = *reinterpret_cast<const uint32_t *>(kxl + ow.w);
     const uint32_t l01 = min(w0, w1), l23 = min(w2, w3), wm = min(l01, l23);
     const int k = k0 + (w0 == wm ? 0 : w1 == wm ? 1 : w2 == wm ? 2 : 3);
-    bool amb = (p[0].s2 >> sh) - (p[0].b >> sh) < (kFastGap + 2u * step_mask) >> sh;
+    bool amb = (p[0].s2 >> bits) - (p[0].b >> bits) < key_gap(kFastGap, bits);
     if constexpr (!EXACT) {
         const uint32_t second = min(min(max(w0, w1), max(w2, w3)), max(l01, l23));
         amb |= second - wm < 3u;
@@ -1200,7 +1205,8 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         }
         return;
     }
-    const int nbat = min(pl.nbat, kMaxBatchLds);    // a multiple of kBatchPad
+    const int nbat = __builtin_amdgcn_readfirstlane(min(pl.nbat, kMaxBatchLds));    // a multiple of kBatchPad
+    const int bits = step_bits(nbat);
 
     // The MFMA rows are the candidate slots: the palette operands of slot j's
     // bin, gathered once and kept in registers for the whole run; distances
@@ -1260,7 +1266,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
         const int nvalid = min(32, n - 32 * t);
         if constexpr (FAST) {
             distances(std::false_type{}, raw, next);
-            if (!search_tile<false, kStepBits>(bt, kx, ky, lane, ip, nvalid, kStepBits, force_exact, out)) {
+            if (!search_tile<false>(bt, kx, ky, lane, ip, nvalid, bits, force_exact, out)) {
                 raw.load(emb + (size_t)ip * dstride, yoff, g);          // this tile's rows again
                 distances(std::true_type{}, raw, []() {});
                 if (tn < tend) raw.load(emb + (size_t)ipn * dstride, yoff, g);   // the next tile's rows again
@@ -1268,7 +1274,7 @@ __global__ __launch_bounds__((kAssignWpb<T, F> * 64)) __attribute__((amdgpu_wave
             }
         } else {
             distances(std::true_type{}, raw, next);
-            if (!search_tile<true, kStepBits>(bt, kx, ky, lane, ip, nvalid, kStepBits, force_exact, out))
+            if (!search_tile<true>(bt, kx, ky, lane, ip, nvalid, bits, force_exact, out))
                 search_exact<127>(bt, kx, ky, lane, ip, nvalid, out);
         }
         t = tn;

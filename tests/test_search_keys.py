@@ -1,0 +1,63 @@
+"""The keys of the assignment search (Eq7), on the CPU: the batch's step takes
+no more low bits of a sum than the frame's batches need, a decided pixel's two
+smallest sums are at least the required binary32 steps apart, and no pair is
+left undecided that lies further apart than the step bits can hide.  The rules
+are the kernels' own header, compiled with g++."""
+import ctypes
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_16874_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("keys")
+    src, so = d / "keys.cpp", d / "keys.so"
+    src.write_text('#include "search_keys.hpp"\nextern "C" {\nint step_bits(int n) { return cpe::step_bits(n); }\n'
+                   'unsigned key_gap(unsigned g, int b) { return cpe::key_gap(g, b); }\n}\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(so), str(src)], check=True)
+    return ctypes.CDLL(str(so))
+
+
+def _constant(name):
+    with open(os.path.join(CSRC, "k_mfma.hpp")) as fh:
+        return int(re.search(rf"constexpr int {name} = (\d+);", fh.read()).group(1))
+
+
+def test_step_bits_are_the_fewest_that_hold_the_steps(rules):
+    for nbat in range(8, 2049, 8):
+        bits = rules.step_bits(nbat)
+        assert 8 << bits >= nbat and (bits == 0 or 8 << (bits - 1) < nbat)
+    assert rules.step_bits(128) == _constant("kStepBits")
+
+
+@pytest.mark.parametrize("nbat", [8, 16, 24, 32, 64, 72, 128, 512, 2048])
+def test_gap_of_decided_pixels(rules, nbat):
+    gap, bits = _constant("kFastGap"), rules.step_bits(nbat)
+    need = rules.key_gap(gap, bits)
+    rng = np.random.default_rng(nbat)
+    reach = 3 * (1 << bits) + 2 * gap
+    s = rng.integers(0x3c000000, 0x44000000, 200000)
+    t = s + rng.integers(0, reach + 1, s.size)
+    step = lambda v: (v >> bits << bits) | rng.integers(0, nbat // 8, v.size)
+    ks, kt = step(s), step(t)
+    decided = (np.maximum(ks, kt) >> bits) - (np.minimum(ks, kt) >> bits) >= need
+    assert (t - s)[decided].min() >= gap                      # the error bound's requirement
+    assert (t - s)[~decided].max() < gap + 3 * (1 << bits)    # what the bits can hide
+    assert ((ks < kt)[decided]).all()                         # the winner's key is the smaller sum
+    if nbat <= 64:                                            # grids of 32 x 32 rarely have more
+        assert decided[t - s >= 16].all()
+
+
+def test_both_assignment_kernels_take_the_frames_bits():
+    for name in ("k_mfma.hpp", "k_assign_big.hpp"):
+        with open(os.path.join(CSRC, name)) as fh:
+            src = fh.read()
+        assert "const int bits = step_bits(nbat);" in src
+        calls = re.findall(r"!search_tile<[^;]*?;", src, flags=re.S) + re.findall(r"!search_tile<.*", src)
+        assert calls and all("nvalid, bits, force_exact" in c for c in calls)
