@@ -16,18 +16,10 @@ namespace cpe {
 // waves) and one assignment workgroup of 12 waves per compute unit.
 constexpr int64_t kVoteGrid = 256;
 constexpr int64_t kAssignGrid = 256;
-// Frames from this many pixels take the fast assignment search when only
-// labels are requested: where a wave has more than one tile the shorter
-// instruction stream pays, below it a near tie's second pass costs more.
-// Measured (exact, fast search, us per frame): 8 harmonics or fewer, 256 x 256
-// fp32 18.5, 19.3; 512 x 512 fp32 25.8, 26.8; 479 x 641 fp16 23.1, 22.8; 704 x
-// 704 fp32 31.8, 31.0; 640 x 640 fp16 26.7, 25.7; above, 512 x 520 fp16 25.2,
-// 25.8; from 2^19 to 2^20 pixels the two are within 1.2 %, either way (900 x
-// 900 46.6, 47.1; 1024 x 1024 53.2, 53.3); 1024 x 2048 61.2, 60.3.
-// fp32 inputs with more than 8 harmonics spill registers in the fast kernel
-// (640 x 640: 38.9, 42.5) and keep the exact one.
+// Inputs that the fast assignment search may serve (fast_search_pixels): no
+// kernel is built for the others.
 template <typename T, int F>
-constexpr int64_t kFastSearchPixels = F <= 8 ? 1LL << 18 : sizeof(T) == 2 ? 1LL << 19 : INT64_MAX;
+constexpr bool kFastSearch = fast_search_pixels(sizeof(T), F) != INT64_MAX;
 
 template <typename T, int F>
 cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
@@ -138,13 +130,14 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
     const bool labels_only = score == nullptr && !(fa.tau4096 < __builtin_inf());
     const double tau32 = fa.tau4096 * 0x1p-7;
     const int32_t force_exact = h->search_mode == 1;
+    const bool fast = kFastSearch<T, F> && labels_only &&
+                      (h->search_mode != 0 || (int64_t)npix >= fast_search_pixels(sizeof(T), F));
     if (mfma) {
         // launch 2: peak extraction in every workgroup's prologue, assignment
         constexpr int wpb2 = kAssignWpb<T, F>;
         const int64_t wgs2 = (tiles + wpb2 - 1) / wpb2;
         const int grid2 = (int)(wgs2 < kAssignGrid ? wgs2 : kAssignGrid);
-        const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels<T, F>);
-        auto assign_kernel = fast ? k_assign_mfma<T, F, true> : k_assign_mfma<T, F, false>;
+        auto assign_kernel = fast ? k_assign_mfma<T, F, kFastSearch<T, F>> : k_assign_mfma<T, F, false>;
         if (!launch(2, assign_kernel, dim3(grid2), dim3(wpb2 * 64), 0, e, dstride, yoff, (const int32_t *)list,
                     (const int32_t *)sc.counts, nslices, slice_px, npix, tau32, h->tb,
                     (const unsigned long long *)hcur, sc.hlast, Bw, Bh, cut, h->cap, cents, num, labels, score,
@@ -167,8 +160,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         if (hipGetLastError() != hipSuccess) return CPE_ERR_HIP;
         const int64_t wgs2 = (tiles + kBigWpb - 1) / kBigWpb;
         const int grid2 = (int)(wgs2 < kAssignGrid ? wgs2 : kAssignGrid);
-        const bool fast = labels_only && (h->search_mode != 0 || (int64_t)npix >= kFastSearchPixels<T, F>);
-        auto assign_kernel = fast ? k_assign_big<T, F, true> : k_assign_big<T, F, false>;
+        auto assign_kernel = fast ? k_assign_big<T, F, kFastSearch<T, F>> : k_assign_big<T, F, false>;
         if (h->stage_on)
             hipExtLaunchKernelGGL(assign_kernel, dim3(grid2), dim3(kBigWpb * 64), 0u, stream, nullptr,
                                   h->stage_ev[5], 0u, e, dstride, yoff, (const int32_t *)list,

@@ -1,6 +1,6 @@
-// search_keys.hpp -- the keys of the assignment's candidate search (search_tile
-// in k_mfma.hpp): the bits of a batch's binary32 distance sum with the batch's
-// step in the low bits.
+// search_keys.hpp -- rules of the assignment's candidate search (search_tile in
+// k_mfma.hpp): its keys, the bits of a batch's binary32 distance sum with the
+// batch's step in the low bits, and the frames that the fast search serves.
 #pragma once
 
 #include <cstdint>
@@ -24,6 +24,28 @@ constexpr int step_bits(int nbat)
 constexpr uint32_t key_gap(uint32_t gap, int bits)
 {
     return (gap + 2u * ((1u << bits) - 1u)) >> bits;
+}
+
+// Frames from this many pixels on take the fast search when only labels are
+// requested (elem: bytes of an input element, F: harmonics): where a wave has
+// more than a tile or two its shorter instruction stream pays, below the longer
+// code fetched cold and a near tie's second pass cost more.  The line lies above
+// the last size at which it measured slower.  Time of a whole frame with the
+// fast search over that with the exact one, 32 x 32 bins:
+//   up to 4 harmonics, both types, from 256 x 256 to 2160 x 3840: 0.94 .. 1.00;
+//   fp32, 5 to 8: 512 x 513 1.02 .. 1.03, 640 x 640 0.99 .. 1.02, 720 x 1024
+//     1.00, 900 x 900 0.98 .. 1.01, 1024 x 1024 0.98 .. 0.99;
+//   fp16, 5 to 9: 512 x 513 0.97 .. 1.01, 512 x 600 0.97 .. 0.98;
+//   fp16, 10 to 16: 640 x 640 0.99 .. 1.02, 720 x 1024 0.99 .. 1.02, 900 x 900
+//     0.98 .. 1.01, 1024 x 1024 0.97 .. 1.00, 1024 x 2048 0.95 .. 0.97;
+//   fp32, 9 to 16: 1.04 .. 1.24 at every size from 479 x 641 to 1500 x 1500
+//     (its registers spill), so it has no such kernel.
+// On 40 x 40 to 96 x 96 bins the ratios at these lines are 0.97 .. 1.00.
+constexpr int64_t fast_search_pixels(int elem, int F)
+{
+    if (F <= 4) return 1LL << 18;
+    if (elem == 2) return F <= 9 ? 9LL << 15 : 1LL << 20;
+    return F <= 8 ? 1LL << 20 : INT64_MAX;
 }
 
 }  // namespace cpe
