@@ -208,9 +208,10 @@ def test_masks_ragged_sizes(H, W):
 
 @pytest.mark.parametrize("H,W", [(1, 15), (1, 17), (19, 53), (9, 112), (1, 1009), (6, 169), (37, 109), (12, 341)])
 def test_masks_piece_edges(H, W):
-    """One pixel less and more than a 16-byte piece and than a wave's 63
-    pieces, several workgroups; 18 masks start at every offset from a 16-byte
-    boundary that H W allows and end inside a group of eight."""
+    """Frames of at most one workgroup's span of 4,096 bytes: one pixel less and
+    more than a 16-byte piece, a few pieces less than a wave's 64 and more;
+    18 masks start at every offset from a 16-byte boundary that H W allows and
+    end inside a group of eight."""
     rng = np.random.default_rng(H * W)
     cap = 20
     dec = native().Decoder(H, W, 1, "f32", np.array([2 * math.pi / W]), np.array([2 * math.pi / H]), 8, 5, cap)
@@ -220,6 +221,30 @@ def test_masks_piece_edges(H, W):
     for first, count in ((1, 18), (0, 9)):
         m = _masks(dec, ld, first, count, H, W)
         assert np.array_equal(m, (lab[None] == (first + 1 + np.arange(count))[:, None, None]).astype(np.uint8))
+    dec.close()
+
+
+@pytest.mark.parametrize("H,W", [(1, 127), (3, 43), (11, 93), (25, 41), (1, 4095), (17, 241), (1, 8191), (1, 8193),
+                                 (127, 129), (59, 347), (479, 641)])
+def test_masks_over_several_spans(H, W):
+    """One pixel less and more than a 128-byte line, a wave's 1,024 bytes, a
+    workgroup's 4,096 and two of them, then frames of several spans: whole
+    waves behind the bytes of the span before, a mask's last bytes in a span of
+    their own.  130 masks start at every offset from a line that H W allows
+    (all 128 for an odd H W)."""
+    rng = np.random.default_rng(H * W)
+    cap = 132
+    dec = native().Decoder(H, W, 1, "f32", np.array([2 * math.pi / W]), np.array([2 * math.pi / H]), 16, 12, cap)
+    lab = rng.integers(-2, cap + 3, size=(H, W)).astype(np.int32)
+    lab.reshape(-1)[-40:] = rng.integers(100, cap, min(40, H * W))
+    ld = torch.from_numpy(lab).cuda()
+    for first, count in ((1, 130), (cap - 9, 9)):
+        print(f"masks {H}x{W} first {first} count {count}", flush=True)
+        m = torch.full((count * H * W + 128,), 7, dtype=torch.uint8, device="cuda")   # a line past the masks' end
+        assert dec.masks(ld, first, count, m) == 0
+        want = ld[None] == torch.arange(first + 1, first + count + 1, dtype=torch.int32, device="cuda")[:, None, None]
+        assert torch.equal(m[:count * H * W].view(count, H, W), want.to(torch.uint8))
+        assert bool((m[count * H * W:] == 7).all())
     dec.close()
 
 
