@@ -53,9 +53,14 @@
  * undefined).  No state carries over between frames -- a frame accumulates
  * its votes into one of two histogram sets, left clear by the frame before
  * it, and its first launch clears the other set for the next frame -- so the
- * next decode on the same handle is unaffected by a failed one.  Data-dependent outcomes (no centroid, more
- * centroids than the capacity) are reported through the device outputs,
- * never as errors.
+ * next decode on the same handle is unaffected by a failed one.
+ * Data-dependent outcomes (no centroid, more centroids than the capacity) are
+ * reported through the device outputs, never as errors.
+ *
+ * Graphs.  A decode on a capturing stream goes into the graph with a launch
+ * that clears a histogram set of its own, so every replay gives what an eager
+ * decode of the buffers' present contents gives, in any order with eager
+ * decodes on the same stream.  The handle must outlive the graph.
  *
  * Threading.  A handle may be used by one stream at a time (its scratch is
  * per handle); separate handles are independent.
@@ -183,7 +188,7 @@ cpe_status cpe_decode_ex(cpe_decoder *h, hipStream_t stream, const void *emb, co
  * forbid hipMalloc): the same frame, arguments, outputs and errors as
  * cpe_decode_ex, and the handle's constants, but the per-frame scratch (vote
  * histograms, participating-pixel list, slice counts, peak list) is a static
- * device array of the library, about 9.7 MB, held by each device the
+ * device array of the library, about 10.2 MB, held by each device the
  * library runs on until the process ends, instead of the handle's.  The
  * call itself allocates nothing.
  *   Limit: frames of at most 2,097,152 pixels (H*W <= 2^21, e.g. 1024 x

@@ -76,8 +76,12 @@ cpe_status decode_frame(cpe_decoder *h, const Scratch *sc, hipStream_t stream, c
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return CPE_ERR_HIP;
     if (dev != h->device) return CPE_ERR_INVALID_ARG;
+    // (the query fails for the default stream, which cannot be captured, while another one is captured)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) capture = hipStreamCaptureStatusNone;
     const FrameArgs fa{stream,       emb,       fg,            fg_threshold, peak_cut(peak_threshold),
-                       tau4096(tau), centroids, num_centroids, labels,       score_map};
+                       tau4096(tau), centroids, num_centroids, labels,       score_map,
+                       capture == hipStreamCaptureStatusActive};
     const Scratch &s = sc ? *sc : h->sc;
     if (h->dtype == CPE_F32) return h->F <= 8 ? launch_f32_lo(h, s, fa) : launch_f32_hi(h, s, fa);
     return h->F <= 8 ? launch_f16_lo(h, s, fa) : launch_f16_hi(h, s, fa);
@@ -101,8 +105,8 @@ double centre_distance(int key, int m)
 constexpr int64_t kStaticMaxPixels = 1LL << 21;     // 2,097,152 pixels, e.g. 1024 x 2048
 constexpr int kStaticMaxBins = kMaxBins * kMaxBins;
 constexpr size_t kStaticSet = (size_t)kReplicas * kStaticMaxBins;                // words per histogram set
-constexpr size_t kStaticHrep = 0;                                               // [2][kReplicas][bins]
-constexpr size_t kStaticHlast = kStaticHrep + 2 * kStaticSet * 8;
+constexpr size_t kStaticHrep = 0;                                               // [kHistSets][kReplicas][bins]
+constexpr size_t kStaticHlast = kStaticHrep + kHistSets * kStaticSet * 8;
 constexpr size_t kStaticPlan = kStaticHlast + (size_t)kStaticMaxBins * 8;
 constexpr size_t kStaticCounts = (kStaticPlan + plan_bytes(kMaxBins, kMaxBins) + 255) & ~(size_t)255;
 constexpr size_t kStaticList = kStaticCounts + (size_t)kMaxSlices * 4;
@@ -335,7 +339,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
     const size_t o_cx = carve(cx.size() * 4), o_cy = carve(cy.size() * 4);
     const size_t o_pop = carve(pop.size() * 2);
     const size_t o_wpk = carve(wt_pk.size() * 2);
-    const size_t o_hrep = carve(2 * (size_t)kReplicas * nb * 8);
+    const size_t o_hrep = carve(kHistSets * (size_t)kReplicas * nb * 8);
     const size_t o_hlast = carve((size_t)nb * 8);
     const size_t o_plan = carve(bins_w > kMfmaBins || bins_h > kMfmaBins ? plan_bytes(bins_w, bins_h) : 0);
     const size_t o_count = carve((size_t)kMaxSlices * 4);

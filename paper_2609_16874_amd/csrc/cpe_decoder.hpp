@@ -13,16 +13,20 @@ namespace cpe {
 
 struct BigPlan;     // k_peaks.hpp
 
+constexpr int kHistSets = 3;
+
 // Per-frame scratch of the launch sequence: everything a decode writes and
 // reads besides the caller's inputs and outputs and the handle's constants.
-// The vote histograms come in two sets of set_stride words each.  A frame
-// accumulates into set *parity, which is clear when the frame starts, and
-// its first launch that runs clears the first dirty[1 - *parity] words of
+// The vote histograms come in three sets of set_stride words each.  A frame
+// accumulates into set *parity (0 or 1), which is clear when the frame starts,
+// and its first launch that runs clears the first dirty[1 - *parity] words of
 // the other set (the ones an earlier frame may have written); *parity flips
 // once that launch is enqueued.  So every frame starts on a clear set, also
-// after a decode that failed part-way.
+// after a decode that failed part-way.  Set 2 belongs to the frames captured
+// into graphs, which clear it themselves: a replay repeats the launches but not
+// the host's steps, so it leaves the other two and their state alone.
 struct Scratch {
-    unsigned long long *hrep;    // [2][set_stride]: per set [kReplicas][nb] vote histograms
+    unsigned long long *hrep;    // [kHistSets][set_stride]: per set [kReplicas][nb] vote histograms
     size_t set_stride;           // words per set (>= kReplicas * nb)
     int *parity;                 // host: the set of the next frame (0 or 1)
     size_t *dirty;               // host: [2] leading words of each set that may be nonzero
@@ -111,6 +115,7 @@ struct FrameArgs {
     cpe_centroid *cents;
     int32_t *num, *labels;
     float *score;
+    bool captured;               // the stream is capturing: the launches go into a graph
 };
 
 // Enqueue the kernels of one frame for element type T and F harmonics, with

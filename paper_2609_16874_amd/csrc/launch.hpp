@@ -57,14 +57,26 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
     };
     const bool mfma = Bw <= kMfmaBins && Bh <= kMfmaBins;     // the matrix-core assignment (and its peak prologue)
     // the frame's histogram set (clear) and the next frame's, whose first
-    // nclear words an earlier frame may have written
+    // nclear words an earlier frame may have written; a captured frame clears
+    // its own set before the vote (Scratch)
+    const bool captured = fa.captured;
     const int par = *sc.parity & 1;
-    unsigned long long *hcur = sc.hrep + (size_t)par * sc.set_stride;
-    unsigned long long *hnext = sc.hrep + (size_t)(1 - par) * sc.set_stride;
-    const size_t nclear = sc.dirty[1 - par];
     const size_t nused = (size_t)kReplicas * nb;
+    unsigned long long *hcur = sc.hrep + (size_t)(captured ? 2 : par) * sc.set_stride;
+    unsigned long long *hnext = captured ? hcur : sc.hrep + (size_t)(1 - par) * sc.set_stride;
+    const size_t nclear = captured ? nused : sc.dirty[1 - par];
+    auto clear_launch = [&]() {
+        const int64_t cg = ((int64_t)nclear + 255) / 256;
+        const int clear_grid = cg < 1 ? 1 : cg > 64 ? 64 : (int)cg;
+        return launch(0, k_clear_u64, dim3(clear_grid), dim3(256), 0, hnext, (int32_t)nclear);
+    };
+    // the vote is about to write the frame's set
+    auto mark = [&]() {
+        if (!captured && sc.dirty[par] < nused) sc.dirty[par] = nused;
+    };
     // once the clearing launch is enqueued: the other set is the next frame's
     auto flip = [&]() {
+        if (captured) return;
         sc.dirty[1 - par] = 0;
         *sc.parity = 1 - par;
     };
@@ -75,9 +87,12 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
     const FusedPlan fp = frame_plan(h);
     if (fp.ok) {
         // Launch 0 would be the compaction, which the vote launch does itself
-        // here: its events record back to back.
+        // here: its events record back to back (a captured frame only clears
+        // its histograms in it).
         if (fail_at == 0) return CPE_ERR_HIP;
-        if (h->stage_on) {
+        if (captured) {
+            if (!clear_launch()) return CPE_ERR_HIP;
+        } else if (h->stage_on) {
             if (hipEventRecord(h->stage_ev[0], stream) != hipSuccess ||
                 hipEventRecord(h->stage_ev[1], stream) != hipSuccess)
                 return CPE_ERR_HIP;
@@ -85,8 +100,8 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         // launch 1: compaction of each workgroup's slices, recovery +
         // voting on them, the next frame's histograms cleared
         const FusedArgs fz{fg, fg_thr, fp.slice, fp.seg_cap, fp.rot, list, sc.counts, labels, score,
-                           hnext, (int32_t)nclear};
-        if (sc.dirty[par] < nused) sc.dirty[par] = nused;
+                           hnext, captured ? 0 : (int32_t)nclear};
+        mark();
         auto vote_kernel = mfma ? k_vote_mfma<T, F, false, true> : k_vote_mfma<T, F, true, true>;
         if (!launch(1, vote_kernel, dim3(fp.grid), dim3(wpb * 64), 0, e, dstride, yoff,
                     (const int32_t *)nullptr, (const int32_t *)nullptr, 0, 0, npix, h->tb, Bw, Bh, hcur, cents,
@@ -99,14 +114,12 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         // launch 0: the participating pixels as a compact list (every pixel
         // when the frame has no foreground channel), the next frame's
         // histograms cleared
-        const int64_t cg = ((int64_t)nclear + 255) / 256;
-        const int clear_grid = cg < 1 ? 1 : cg > 64 ? 64 : (int)cg;
         nslices = slice_count(npix);
         slice_px = slice_pixels(npix);
         if (!g) list = nullptr;
         bool ok;
         if (!g)
-            ok = launch(0, k_clear_u64, dim3(clear_grid), dim3(256), 0, hnext, (int32_t)nclear);
+            ok = clear_launch();
         else if (((uintptr_t)g & 15u) == 0)
             ok = launch(0, k_compact<T, true>, dim3(nslices), dim3(kCompactThreads), 0, g, npix, fg_thr, list,
                         sc.counts, labels, score, hnext, (int32_t)nclear);
@@ -120,7 +133,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
         const int64_t wgs = (tiles + wpb - 1) / wpb;
         const int grid = (int)(wgs < kVoteGrid ? wgs : kVoteGrid);
         auto vote_kernel = mfma ? k_vote_mfma<T, F, false, false> : k_vote_mfma<T, F, true, false>;
-        if (sc.dirty[par] < nused) sc.dirty[par] = nused;
+        mark();
         if (!launch(1, vote_kernel, dim3(grid), dim3(wpb * 64), 0, e, dstride, yoff, (const int32_t *)list,
                     (const int32_t *)sc.counts, nslices, slice_px, npix, h->tb, Bw, Bh, hcur, cents, h->cap,
                     FusedArgs{}))
