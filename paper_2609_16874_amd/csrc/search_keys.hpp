@@ -14,9 +14,7 @@ namespace cpe {
 // to 16 with the 3 of 64.
 constexpr int step_bits(int nbat)
 {
-    int bits = 0;
-    while ((8 << bits) < nbat) bits++;
-    return bits;
+    return nbat > 8 ? 32 - __builtin_clz((uint32_t)(nbat - 1) >> 3) : 0;
 }
 
 // Difference of two sums, each shifted right by `bits`, from which on the sums
