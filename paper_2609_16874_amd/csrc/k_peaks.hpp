@@ -30,10 +30,6 @@ namespace cpe {
 
 typedef uint32_t u32x4_pk __attribute__((ext_vector_type(4)));
 
-// Strict local maxima of a B_w x B_h grid are pairwise non-adjacent, so there
-// are at most ceil(B_w / 2) * ceil(B_h / 2) of them.
-__host__ __device__ constexpr int max_peaks(int Bw, int Bh) { return ((Bw + 1) / 2) * ((Bh + 1) / 2); }
-
 // ---------------------------------------------------------------------------
 // Grids up to 32 x 32: candidates in LDS, in the assignment kernel's prologue
 // ---------------------------------------------------------------------------
@@ -212,10 +208,10 @@ __device__ __forceinline__ void peaks_lds_find(const PeakBins<WAVES> &pb, long l
 // then the batches' column offsets (16 bytes each), row offsets and first
 // candidates (4 bytes each), arrays of max_batches() + kBatchPad entries.
 struct BigPlan {
-    int32_t K, Kc;                // candidates; min(K, cap)
+    int32_t Kc;                   // min(K, cap) candidates
     int32_t nbat, nbat_real;      // batches with and without the padding
     int32_t ncol, nrow;           // candidate columns and rows
-    int32_t reserved[2];
+    int32_t reserved[3];
     uint8_t colbin[kMaxBins], rowbin[kMaxBins];   // bins of the column and row slots (ascending)
 };
 static_assert(sizeof(BigPlan) % 16 == 0, "the batch offsets follow, 16-byte aligned");
@@ -391,7 +387,7 @@ __global__ __launch_bounds__(1024) __attribute__((unused)) void k_peaks(const un
             bk[total + lane] = 0u;
         }
         if (lane == 0) {
-            plan->K = *num = K;
+            *num = K;
             plan->Kc = min(K, cap);
             plan->nbat = padded;
             plan->nbat_real = total;
