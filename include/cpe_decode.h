@@ -187,7 +187,7 @@ cpe_status cpe_decode_ex(cpe_decoder *h, hipStream_t stream, const void *emb, co
  * decode (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same frame, arguments, outputs and errors as
  * cpe_decode_ex, and the handle's constants, but the per-frame scratch (vote
- * histograms, participating-pixel list, slice counts, peak list) is a static
+ * histograms, participating-pixel list, slice counts, plan) is a static
  * device array of the library, about 10.2 MB, held by each device the
  * library runs on until the process ends, instead of the handle's.  The
  * call itself allocates nothing.
@@ -251,11 +251,13 @@ cpe_status cpe_decode_get_histogram(cpe_decoder *h, hipStream_t stream, uint64_t
 
 /*
  * Self-check (tests): enqueue on `stream` a comparison of the square root the
- * assignment uses (the hardware square root plus a rounding correction) with
+ * assignment uses (the hardware's reciprocal root with one correction) with
  * the IEEE correctly rounded sqrtf on every binary32 value it can receive
- * (0 and every float in [1, 2^32)); the device uint64 *mismatches (8-byte
- * aligned, caller-owned) receives the number of differing results, 0 when
- * the assignment's distances are exactly those of Eq4 as defined above.
+ * (0 and every float in [1, 2^32), also scaled by 2^-14), and of the hardware
+ * root that the fast search uses, which must be within one step of it; the
+ * device uint64 *mismatches (8-byte aligned, caller-owned) receives the number
+ * of values that fail, 0 when the assignment's distances are exactly those of
+ * Eq4 as defined above.
  */
 cpe_status cpe_check_sqrt(hipStream_t stream, unsigned long long *mismatches);
 

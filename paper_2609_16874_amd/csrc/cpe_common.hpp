@@ -17,7 +17,7 @@ constexpr int kReplicas = 4;          // replicated global histograms (spread of
 constexpr int kMaxF = 16;             // harmonics per axis
 constexpr int kMaxBins = 128;
 constexpr int kCountCap = 1024;       // centroids whose pixel counts are privatised in LDS
-constexpr int kMfmaBins = 32;         // bin grids up to 32 x 32 take the matrix-core path
+constexpr int kMfmaBins = 32;         // side of a block of bins; grids of one block are assigned without a peak kernel
 constexpr int kDistBase = 158;        // palette split of the matrix-core distances (head of k_mfma.hpp)
 constexpr int kPopKinds = 7;          // binary16 palette operand kinds per axis (Tables::pop)
 constexpr int kMaxBinBlocks = (kMaxBins + kMfmaBins - 1) / kMfmaBins;   // blocks of 32 bins per axis
@@ -42,12 +42,11 @@ struct Tables {
 
 // The correctly rounded binary32 square root of x, 0 or at least 2^-20: the
 // Eq4 distance from x = fl32(S), also scaled by 2^-14.  y is the hardware's
-// reciprocal root, s = x y is within a few units of the root in the last place, its
-// residual x - s^2 is exact, and one multiply-add by y / 2 rounds s plus the
-// first-order correction once.  What that leaves is below 2^-22 units before
-// the rounding, more than separates some roots from a midpoint, so that the
-// result is right for every input is a matter of trial: cpe_check_sqrt tries
-// them all.  For x = 0, s and the residual are 0.  (The hardware root with its
+// reciprocal root; s = x y is corrected to first order by its residual x - s^2
+// times y / 2, with one rounding of each multiply-add.  No bound on the
+// hardware's root proves the result: that it is correctly rounded for every
+// input rests on trial alone, cpe_check_sqrt tries them all.  For x = 0, s and
+// the residual are 0.  (The hardware root with its
 // two neighbours tested by residuals takes three instructions more: 28.5 against
 // 27.7 us for a 640 x 640 fp16 frame with 16 harmonics, 92.2 against 89.4 us for
 // 1024 x 2048 with the score map.)

@@ -7,9 +7,10 @@
 //
 // Launches per frame on the caller's stream (launch.hpp), no allocation, no
 // host synchronisation, no host copy:
-//   compact participating-pixel list, vote histograms cleared (k_compact);
+//   compact participating-pixel list, vote histograms cleared (k_compact, frames
+//           above 2^21 pixels; the vote launch does it in smaller ones);
 //   vote    per-pixel recovery + soft voting into replicated 64-bit histograms
-//           (k_vote_mfma, one pass per block of 32 x 32 bins);
+//           (k_vote_mfma, one pass up to 32 x 32 bins);
 //   peaks   local-maxima search and the assignment's plan (k_peaks, grids
 //           above 32 x 32);
 //   assign  nearest-candidate assignment, label and score write-out, pixel
@@ -329,7 +330,7 @@ cpe_status cpe_decode_create(cpe_decoder **out, int32_t H, int32_t W, int32_t D,
             }
     }
 
-    // one allocation: constants, replicated histograms, last histogram, peak list, counters
+    // one allocation: constants, replicated histograms, last histogram, plan, counters, list
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t o = off;

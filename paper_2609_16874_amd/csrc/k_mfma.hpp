@@ -1,12 +1,13 @@
-// k_mfma.hpp -- matrix-core decoder kernels: the vote for every bin grid (in
-// passes over blocks of 32 x 32 bins), the assignment for grids up to 32 x 32.
+// k_mfma.hpp -- matrix-core decoder kernels: the vote for every bin grid (above
+// 32 x 32 in passes of two x blocks and one y block of 32 bins), the assignment
+// for grids up to 32 x 32.
 //
 // Both passes stream a compact list of participating pixels (or every
 // pixel, when the frame has no foreground channel), cut into tiles of 32
-// consecutive entries.  The assignment, and the vote of three-launch
-// frames, read the list in global memory (written by k_compact, or by the
-// vote launch in two-launch frames): every workgroup gets a contiguous run
-// of tiles of the same length to within one.  In two-launch frames the vote
+// consecutive entries.  The assignment, and the vote of frames above
+// kFusedMaxPixels, read the list in global memory (written by k_compact, or by
+// the vote launch of smaller frames): every workgroup gets a contiguous run
+// of tiles of the same length to within one.  In smaller frames the vote
 // lists its own share of the pixels in LDS (FusedArgs).  The waves take
 // their tiles one at a time from a counter in LDS (so that they finish
 // together however the SIMDs favour older waves), always loading the
@@ -507,7 +508,7 @@ constexpr int vote_wpb(bool multi)
 // pass loop).  Each pass converts the input and weighs the y block anew, so
 // two x blocks per pass take 3 weight sets and one conversion where single
 // blocks take 4 and 2 (704 x 704 fp32 with 4 harmonics, 64 x 64 bins: 31.3
-// against 40.3 us).
+// against 40.3 us on a list made before the launch; 34.2 with the compaction).
 // FUSED: the launch lists the participating pixels itself (FusedArgs); list
 // and counts are then unused.
 template <typename T, int F, bool MULTI, bool FUSED>

@@ -13,7 +13,7 @@
 namespace cpe {
 
 // Grid caps of the matrix-core kernels: one resident vote workgroup (8 or 12
-// waves) and one assignment workgroup of 12 waves per compute unit.
+// waves) and one assignment workgroup (12 or 16) per compute unit.
 constexpr int64_t kVoteGrid = 256;
 constexpr int64_t kAssignGrid = 256;
 // Inputs that the fast assignment search may serve (fast_search_pixels): no
@@ -128,8 +128,8 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
                         sc.counts, labels, score, hnext, (int32_t)nclear);
         if (!ok) return CPE_ERR_HIP;
         flip();
-        // launch 1: recovery + voting, in passes over blocks of 32 x 32 bins;
-        // grid: at most one workgroup per compute unit, no more waves than tiles
+        // launch 1: recovery + voting, above 32 x 32 bins in passes of two x
+        // blocks and one y block of 32 bins each; grid: at most one workgroup per compute unit, no more waves than tiles
         const int64_t wgs = (tiles + wpb - 1) / wpb;
         const int grid = (int)(wgs < kVoteGrid ? wgs : kVoteGrid);
         auto vote_kernel = mfma ? k_vote_mfma<T, F, false, false> : k_vote_mfma<T, F, true, false>;

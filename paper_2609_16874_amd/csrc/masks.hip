@@ -148,7 +148,8 @@ cpe_status launch_masks(hipStream_t stream, const int32_t *labels, int64_t npix,
     auto launch = [&](auto kernel, int64_t bytes) {
         // a multiple of eight workgroups per group of masks: workgroups go to
         // the eight XCDs in turn, so that every group's workgroup of a span
-        // finds its labels in the same L2
+        // finds its labels in the same L2 (1025 x 2047, 64 masks: 28.2 us with
+        // 513 workgroups, 23.1 with 520)
         const int64_t spans = (bytes + kMaskSpan - 1) / kMaskSpan;
         const dim3 grid((unsigned)((spans + 7) / 8 * 8), groups);
         hipLaunchKernelGGL(kernel, grid, dim3(kMaskThreads), 0, stream, labels, npix, first, count, masks);

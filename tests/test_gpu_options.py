@@ -7,8 +7,8 @@ ABI, against the CPU oracle.
   (the strict test decides pixels sitting exactly on it) and half a unit of
   1/4096 above; tau = 0 and tau = inf.
 * cpe_decode_ex without a foreground channel: every pixel votes and is
-  labelled (the participating set of Section 3.1), on the matrix-core and the
-  generic kernels.
+  labelled (the participating set of Section 3.1), on grids up to and above
+  32 x 32 bins.
 * cpe_decode_masks: the binary masks of Eq8 equal labels == k + 1 byte for
   byte, for aligned and ragged frame sizes, sub-ranges and indices past K.
 Bit-exact on histogram, centroids, counts and labels; the score map within
@@ -72,7 +72,7 @@ def _workload(cfg, bins=None):
     return spec, th, synth.make_frame(cfg), bins or spec.bins
 
 
-# (workload, bins or None for its own grid): matrix-core f32 and f16, generic
+# (workload, bins or None for its own grid): f32 and f16 up to 32 x 32 bins, 64 x 64
 @pytest.mark.parametrize("cfg,bins", [(1, None), (2, None), (5, 64)])
 def test_mask_threshold_parity(cfg, bins):
     spec, th, f, b = _workload(cfg, bins)
@@ -305,7 +305,7 @@ def test_decode_after_a_failed_one_matches_the_oracle(bins, fail):
     """A decode that stops before one of its launches (the test hook reports
     it as a failed launch, CPE_ERR_HIP, after enqueueing the launches before
     it) leaves nothing behind: the next decode on the same handle, of another
-    frame, equals the oracle bit for bit.  Matrix-core and generic kernels."""
+    frame, equals the oracle bit for bit.  Grids up to and above 32 x 32."""
     nat = native()
     spec = synth.CONFIGS[1]
     fx, fy = spec.freqs()

@@ -104,8 +104,8 @@ def test_workload_parity(cfg):
 def test_paper_shape_bin_sweep_parity(bins):
     """The paper's own decoder shape (704x704, L = 4 harmonics, fp32) at every
     bin count of its Table 1 sweep, with the thresholds calibrated per grid:
-    grids up to 32x32 take the matrix-core kernels, larger ones the generic
-    kernels and the stand-alone peak kernel."""
+    grids up to 32x32 extract the peaks in the assignment, larger ones in the
+    stand-alone peak kernel."""
     spec = synth.CONFIGS[5]
     with open(GOLDEN) as fh:
         th = json.load(fh)["sweep"][str(bins)]

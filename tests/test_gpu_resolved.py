@@ -3,9 +3,9 @@
 The embedding keeps all its channels (D = 4 x the encoding's harmonics) and
 the decoder is built for its first n harmonics only: the matrix-core kernels
 read the 8-channel slices of n = 4 as 16-byte vectors from each axis block,
-n = 2 and n = 1 take the scalar path, n = 8 of a 16-harmonic encoding reads
-whole blocks at a y offset of D/2, and a 48 x 48 grid takes the generic
-kernels.  Thresholds: the frozen resolved-decode thresholds for the
+n = 2 and n = 1 read 8- and 4-byte words, n = 8 of a 16-harmonic encoding reads
+whole blocks at a y offset of D/2, and a 48 x 48 grid takes the kernels of
+larger grids.  Thresholds: the frozen resolved-decode thresholds for the
 workloads' own grids, 0.1 x the oracle's largest vote mass otherwise.
 Bit-exact on histogram, records, K and labels; the score map within 1e-5
 relative.

@@ -61,7 +61,7 @@ def test_noalloc_equals_decode_ex_on_two_calls_in_a_row():
                   20, 0.3, math.inf))
     f1 = synth.make_frame(1)
     cases.append((f1.spec, f1.emb, None, 32, 30.0, 5.4))
-    # then the 256x256 workload on a 48 x 48 grid (the generic kernels, more
+    # then the 256x256 workload on a 48 x 48 grid (the kernels of larger grids, more
     # histogram words than any grid above), and the 640x640 one again: each
     # call starts on histograms the calls before it left clear
     theta48 = 2.5 * (48 / 32.0) ** -2
