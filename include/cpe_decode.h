@@ -57,10 +57,11 @@
  * Data-dependent outcomes (no centroid, more centroids than the capacity) are
  * reported through the device outputs, never as errors.
  *
- * Graphs.  A decode on a capturing stream goes into the graph with a launch
- * that clears a histogram set of its own, so every replay gives what an eager
- * decode of the buffers' present contents gives, in any order with eager
- * decodes on the same stream.  The handle must outlive the graph.
+ * Graphs.  cpe_decode, cpe_decode_ex and cpe_decode_noalloc on a capturing
+ * stream go into the graph with a launch that clears a histogram set kept for
+ * captured frames, so every replay gives what an eager decode of the buffers'
+ * present contents gives, in any order with eager decodes on the same stream.
+ * The handle must outlive the graph.
  *
  * Threading.  A handle may be used by one stream at a time (its scratch is
  * per handle); separate handles are independent.
