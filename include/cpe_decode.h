@@ -275,9 +275,10 @@ cpe_status cpe_decode_test_fail_launch(cpe_decoder *h, int32_t launch);
  * Testing: the assignment search of later label-only decodes on this handle
  * (no score map, tau = +inf).  mode 0 (default): the fast search (hardware
  * square roots, near ties recomputed exactly) on frames of at least 2^18
- * pixels with up to 4 harmonics; for binary16 inputs 9 2^15 with 5 to 9 and
- * 2^20 with more; for binary32 ones 2^20 with 5 to 8; the exact search
- * otherwise, for binary32 inputs with more than 8 harmonics in every mode.
+ * pixels with up to 4 harmonics or without a foreground plane; else for
+ * binary16 inputs 9 2^15 with 5 to 9 and 2^20 with more, for binary32 ones 2^20;
+ * the exact search otherwise, for binary32 inputs with more than 8 harmonics in
+ * every mode.
  * 1: the fast-search kernel at any size with every tile treated as a near tie,
  * i.e. recomputed with correctly rounded distances and the exact search;
  * 2: the fast search at any size.  The labels are the same in every mode.

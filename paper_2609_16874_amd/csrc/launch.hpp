@@ -19,7 +19,7 @@ constexpr int64_t kAssignGrid = 256;
 // Inputs that the fast assignment search may serve (fast_search_pixels): no
 // kernel is built for the others.
 template <typename T, int F>
-constexpr bool kFastSearch = fast_search_pixels(sizeof(T), F) != INT64_MAX;
+constexpr bool kFastSearch = fast_search_pixels(sizeof(T), F, true) != INT64_MAX;
 
 template <typename T, int F>
 cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
@@ -144,7 +144,7 @@ cpe_status launch_all(cpe_decoder *h, const Scratch &sc, const FrameArgs &fa)
     const double tau32 = fa.tau4096 * 0x1p-7;
     const int32_t force_exact = h->search_mode == 1;
     const bool fast = kFastSearch<T, F> && labels_only &&
-                      (h->search_mode != 0 || (int64_t)npix >= fast_search_pixels(sizeof(T), F));
+                      (h->search_mode != 0 || (int64_t)npix >= fast_search_pixels(sizeof(T), F, g != nullptr));
     if (mfma) {
         // launch 2: peak extraction in every workgroup's prologue, assignment
         constexpr int wpb2 = kAssignWpb<T, F>;

@@ -25,11 +25,12 @@ constexpr uint32_t key_gap(uint32_t gap, int bits)
 }
 
 // Frames from this many pixels on take the fast search when only labels are
-// requested (elem: bytes of an input element, F: harmonics): where a wave has
-// more than a tile or two its shorter instruction stream pays, below the longer
-// code fetched cold and a near tie's second pass cost more.  The line lies above
-// the last size at which it measured slower.  Time of a whole frame with the
-// fast search over that with the exact one, 32 x 32 bins:
+// requested (elem: bytes of an input element, F: harmonics, plane: there is a
+// foreground plane): where a wave has more than a tile or two its shorter
+// instruction stream pays, below the longer code fetched cold and a near tie's
+// second pass cost more.  The line lies above the last size at which it measured
+// slower.  Time of a whole frame with the fast search over that with the exact
+// one, 32 x 32 bins, 30 to 60 % of the pixels foreground:
 //   up to 4 harmonics, both types, from 256 x 256 to 2160 x 3840: 0.94 .. 1.00;
 //   fp32, 5 to 8: 512 x 513 1.02 .. 1.03, 640 x 640 0.99 .. 1.02, 720 x 1024
 //     1.00, 900 x 900 0.98 .. 1.01, 1024 x 1024 0.98 .. 0.99;
@@ -39,11 +40,13 @@ constexpr uint32_t key_gap(uint32_t gap, int bits)
 //   fp32, 9 to 16: 1.04 .. 1.24 at every size from 479 x 641 to 1500 x 1500
 //     (its registers spill), so it has no such kernel.
 // On 40 x 40 to 96 x 96 bins the ratios at these lines are 0.97 .. 1.00.
-constexpr int64_t fast_search_pixels(int elem, int F)
+// Without a plane every pixel is searched, twice the tiles or more: 256 x 256 0.98
+// .. 1.03, 512 x 513 and above 0.93 .. 1.00 for every harmonic count.
+constexpr int64_t fast_search_pixels(int elem, int F, bool plane)
 {
-    if (F <= 4) return 1LL << 18;
-    if (elem == 2) return F <= 9 ? 9LL << 15 : 1LL << 20;
-    return F <= 8 ? 1LL << 20 : INT64_MAX;
+    if (elem == 4 && F > 8) return INT64_MAX;
+    if (F <= 4 || !plane) return 1LL << 18;
+    return elem == 2 && F <= 9 ? 9LL << 15 : 1LL << 20;
 }
 
 }  // namespace cpe

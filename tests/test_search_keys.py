@@ -20,7 +20,8 @@ def rules(tmp_path_factory):
     src, so = d / "keys.cpp", d / "keys.so"
     src.write_text('#include "search_keys.hpp"\nextern "C" {\nint step_bits(int n) { return cpe::step_bits(n); }\n'
                    'unsigned key_gap(unsigned g, int b) { return cpe::key_gap(g, b); }\n'
-                   'long long fast_search_pixels(int e, int f) { return cpe::fast_search_pixels(e, f); }\n}\n')
+                   'long long fast_search_pixels(int e, int f, int p)\n'
+                   '{ return cpe::fast_search_pixels(e, f, p); }\n}\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(so), str(src)], check=True)
     lib = ctypes.CDLL(str(so))
     lib.fast_search_pixels.restype = ctypes.c_longlong
@@ -75,10 +76,20 @@ SLOWER = [(4, 5, 512 * 513), (4, 6, 640 * 640), (4, 7, 512 * 600), (4, 8, 512 * 
 FASTER = [(4, 2, 704 * 704), (4, 4, 512 * 513), (4, 5, 1100 * 1100), (4, 8, 1500 * 1500), (2, 2, 640 * 640),
           (2, 4, 512 * 512), (2, 7, 512 * 600), (2, 8, 512 * 600), (2, 9, 512 * 600), (2, 10, 1100 * 1100),
           (2, 12, 1100 * 1100), (2, 16, 1024 * 2048)]
+# the same for frames without a foreground plane
+SLOWER_WITHOUT_PLANE = [(4, 5, 256 * 256), (4, 8, 256 * 256), (4, 9, 1024 * 2048), (2, 6, 256 * 256), (2, 9, 256 * 256),
+                        (2, 16, 256 * 256)]
+FASTER_WITHOUT_PLANE = [(4, 4, 512 * 513), (4, 5, 640 * 640), (4, 6, 479 * 641), (4, 7, 479 * 641), (2, 5, 512 * 513),
+                        (2, 8, 512 * 513), (2, 9, 479 * 641), (2, 10, 512 * 513), (2, 12, 640 * 640),
+                        (2, 16, 640 * 640)]
 
 
 def test_fast_search_follows_the_measurements(rules):
     for elem, F, pixels in SLOWER:
-        assert pixels < rules.fast_search_pixels(elem, F), (elem, F, pixels)
+        assert pixels < rules.fast_search_pixels(elem, F, 1), (elem, F, pixels)
     for elem, F, pixels in FASTER:
-        assert pixels >= rules.fast_search_pixels(elem, F), (elem, F, pixels)
+        assert pixels >= rules.fast_search_pixels(elem, F, 1), (elem, F, pixels)
+    for elem, F, pixels in SLOWER_WITHOUT_PLANE:
+        assert pixels < rules.fast_search_pixels(elem, F, 0), (elem, F, pixels)
+    for elem, F, pixels in FASTER_WITHOUT_PLANE:
+        assert pixels >= rules.fast_search_pixels(elem, F, 0), (elem, F, pixels)
