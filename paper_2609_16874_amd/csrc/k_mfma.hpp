@@ -172,8 +172,8 @@ __device__ __forceinline__ v2s twice_x(f16x2 x)
 // Raw input words of one lane's operand slices: for each axis and K-step j
 // the 8 channels [16 j + 8 g, 16 j + 8 g + 8) of one pixel's axis block.
 // Loaded one tile ahead of their use, so the load only moves them: a lane of
-// half 1 whose channels lie past the block holds the block's first ones
-// instead, which convert() leaves out of |X|^2 and the palette's zeros out of
+// half 1 whose channels lie past the block holds those of half 0 instead, which
+// convert() leaves out of |X|^2 and the palette's zeros out of
 // the products.  (Zeroing them here makes the load wait for its data at once:
 // 165.6 against 149.4 us per frame at 1500 x 1600 fp32 with 12 harmonics, 80.7
 // against 76.5 at fp16 with 4, 31.9 against 31.2 at 704 x 704 fp32 with 4.)
@@ -206,8 +206,7 @@ struct RawSlices {
                     const int c0 = 16 * j + kG * q;            // of half 0; half 1's is 8 further
                     if (c0 >= C) continue;                     // of neither half: never read
                     uint32_t *dst = &w[ax][j][q * kGB / 4];
-                    const bool on = c0 + 8 < C || g == 0;
-                    const T *src = row + ax * yoff + (on ? c0 + 8 * g : 0);
+                    const T *src = row + ax * yoff + (c0 + 8 < C ? c0 + 8 * g : c0);
 #pragma unroll
                     for (int k = 0; k < kGB / kLoad; k++) {
                         typedef uint32_t vec __attribute__((ext_vector_type(kLoad / 4)));
